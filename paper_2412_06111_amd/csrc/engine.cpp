@@ -71,7 +71,7 @@ int position_of_mode(const std::vector<Pos>& ps, int mode) {
 void left_op(Plan& P, GemmArgs g, double* dst, int mode, double alpha, hipStream_t st) {
   g.right = false;
   const int64_t rows = g.L * g.Q;
-  g.nchunks = pick_chunks(rows, g.ncols, g.n, P.partial_elems);
+  g.nchunks = pick_chunks(g, P.partial_elems);
   if (g.nchunks == 1 && mode == 2) {
     g.out = dst;
     g.out_f32 = false;
@@ -329,7 +329,7 @@ void record_box(Plan& P, const void* block, const int64_t* off, const int64_t* e
   auto left = [&](GemmArgs g, double* dst, int mode, double a) {
     g.right = false;
     const int64_t rows = g.L * g.Q;
-    g.nchunks = pick_chunks(rows, g.ncols, g.n, P.partial_elems);
+    g.nchunks = pick_chunks(g, P.partial_elems);
     g.out_f32 = false;
     BoxOp op;
     if (g.nchunks == 1 && mode == 2) {
@@ -417,7 +417,7 @@ void record_box(Plan& P, const void* block, const int64_t* off, const int64_t* e
     a.amap = amap;
     a.bmap = bmap;
     if (pre.empty()) a.hm = raw_hmap(P, ext, strides, p0, w);
-    a.nchunks = pick_chunks(a.n, a.ncols, a.L * a.Q, P.partial_elems);
+    a.nchunks = pick_chunks(a, P.partial_elems);
     a.out = P.partial;
     a.ol = OutLayout{INT64_MAX, a.ncols, 1, 0, a.n * a.ncols};
     op.reduce = true;
@@ -748,7 +748,7 @@ void update_box_impl(Plan& P, const void* block, const int64_t* off, const int64
     a.ncols = t.r;
     a.amap = amap;
     a.bmap = bmap;
-    a.nchunks = pick_chunks(a.n, a.ncols, a.L * a.Q, P.partial_elems);
+    a.nchunks = pick_chunks(a, P.partial_elems);
     a.out = P.partial;
     a.ol = OutLayout{INT64_MAX, a.ncols, 1, 0, a.n * a.ncols};
     const int nch = launch_gemm(a, st);

@@ -1,6 +1,6 @@
 // Generic contraction kernels of the engine (any tree, any box, any dtype).
 //
-// One LDS-tiled FP64 kernel covers both contractions the method needs on a
+// One LDS-tiled kernel (gemm_tile.hpp) covers both contractions the method needs on a
 // 3-index view H[L][n][Q] of a (partially contracted) tensor:
 //   RIGHT  R(i, j)    = sum_{l,q} H[l, i, q] X[row(l, q), j]   (right sketch T^{t} X_t,
 //                                                           Sec. 4; STTNN on T_{S_t}, Sec. 5)
@@ -14,431 +14,35 @@
 #include <cstring>
 #include <map>
 #include <mutex>
-#include <type_traits>
+#include <tuple>
 
-#include "kernels.hpp"
-#include "mfma.hpp"
+#include "gemm_tile.hpp"
 
 namespace ttnn {
 namespace {
 
-constexpr int BR = 64;   // output rows per block
-constexpr int BJ = 32;   // output columns per block
-constexpr int BK = 16;   // contraction step
+constexpr int kTargetBlocks = 768;    // workgroups a contraction is split for: one round of three a compute unit
+constexpr int kMinSteps = 8;          // and the least steps a chunk is worth (below, a tile's
+                                      // descriptor, tables and first loads outweigh its steps)
 
-template <typename T> __device__ inline double ld(const T* p, int64_t i) { return to_f64(p[i]); }
-__device__ inline float ldf(const float* p, int64_t i) { return p[i]; }
-__device__ inline float ldf(const uint16_t* p, int64_t i) { return bf16_bits_to_f32(p[i]); }
-
-// The tile's inner product on the 16x16x4 MFMA of the compute type CT: FP32 for FP32 /
-// BF16 operands (FP32 accumulation within the chunk; the chunk partial is written in
-// the output type and chunks are summed in FP64 by the reduction), FP64 when either
-// operand is FP64.  Each of the 4 waves owns 16 rows and both 16-column blocks.  A VALU
-// form (four rows by two columns a thread) reads six LDS words per eight FMAs and is
-// bound by LDS bandwidth; an MFMA reads one word a lane per 1024 FMAs (FP32) or 512
-// (FP64), and the FP64 MFMA's peak equals the FP64 vector units'.
-template <typename CT> __device__ inline CT ldc(const float* p, int64_t i) { return static_cast<CT>(p[i]); }
-template <typename CT> __device__ inline CT ldc(const uint16_t* p, int64_t i) {
-  return static_cast<CT>(bf16_bits_to_f32(p[i]));
-}
-template <typename CT> __device__ inline CT ldc(const double* p, int64_t i) { return static_cast<CT>(p[i]); }
-
-template <bool RIGHT, typename TH, typename TD, typename TO, typename CT = float>
-__device__ __forceinline__ void gemm_tile_mfma(const TH* __restrict__ H, int64_t L, int64_t n, int64_t Q,
-                                               const TD* __restrict__ D, int64_t sDr, int64_t sDc, int ncols,
-                                               const IndexMap& amap, const IndexMap& bmap, const HMap& hm,
-                                               int64_t kchunk, TO* __restrict__ out, const OutLayout& ol,
-                                               int64_t row0, int64_t c, int j0) {
-  // operand and DRM entries of step s + 1 are loaded into registers (and the DRM rows
-  // of step s + 2 computed) while step s is multiplied out of LDS
-  using P = Pol<std::is_same_v<CT, double> ? TTNN_F64 : TTNN_F32>;
-  constexpr int NA = BR * BK / 256, NB = BK * BJ / 256;
-  __shared__ CT As[BK][BR + 4];
-  __shared__ CT Bs[BK][BJ + 4];
-  __shared__ int64_t drow[2][BK];
-
-  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
-  const int wave = tid >> 6;
-  const int64_t rows_total = RIGHT ? n : L * Q;
-  const int64_t K = RIGHT ? L * Q : n;
-  const int64_t k_begin = c * kchunk;
-  const int64_t k_end = (k_begin + kchunk < K) ? k_begin + kchunk : K;
-  const bool kk_contig = RIGHT ? (L > 1) : (L == 1);
-  typename P::CFrag acc[BJ / 16];
-#pragma unroll
-  for (int cb = 0; cb < BJ / 16; ++cb) acc[cb] = typename P::CFrag{};
-
-  auto drm_row = [&](int64_t kk) -> int64_t {
-    if (kk >= k_end) return -1;
-    return RIGHT ? amap(kk % L) + bmap(kk / L) : amap(kk);
-  };
-  auto a_pos = [&](int e, int& kk, int& rr) {
-    if (kk_contig) {
-      kk = e % BK;
-      rr = e / BK;
-    } else {
-      rr = e % BR;
-      kk = e / BR;
-    }
-  };
-  CT ra[NA], rb[NB];
-  auto fetch = [&](int64_t kb, int buf) {
-#pragma unroll
-    for (int s = 0; s < NA; ++s) {
-      int kk, rr;
-      a_pos(tid + 256 * s, kk, rr);
-      const int64_t kg = kb + kk;
-      const int64_t rg = row0 + rr;
-      CT v = 0;
-      if (kg < k_end && rg < rows_total) {
-        const int64_t m = RIGHT ? kg : rg;
-        const int64_t i = RIGHT ? rg : kg;
-        const int64_t l = m % L;
-        const int64_t q = m / L;
-        v = ldc<CT>(H, hm(l, i, q, L, n));
-      }
-      ra[s] = v;
-    }
-#pragma unroll
-    for (int s = 0; s < NB; ++s) {
-      const int e = tid + 256 * s;
-      const int jj = e % BJ;
-      const int kk = e / BJ;
-      const int64_t r = drow[buf][kk];
-      rb[s] = (r >= 0 && j0 + jj < ncols) ? ldc<CT>(D, r * sDr + static_cast<int64_t>(j0 + jj) * sDc) : CT(0);
-    }
-  };
-
-  if (tid < BK) {
-    drow[0][tid] = drm_row(k_begin + tid);
-    drow[1][tid] = drm_row(k_begin + BK + tid);
+// The kernels of a contraction's operand types: the raw block with the compute-type maps,
+// or an FP64 intermediate with the FP64 maps; FP32 results only from the reconstruction.
+LaunchTiles tiles_for(bool right, int th, int td, bool out_f32) {
+  TTNN_REQUIRE(th == td, TTNN_E_INVALID, "contraction operands of different types");
+  const TileKernels k = th == TTNN_F64 ? tile_kernels_f64() : th == TTNN_F32 ? tile_kernels_f32() : tile_kernels_bf16();
+  if (out_f32) {
+    TTNN_REQUIRE(!right && k.left_f32, TTNN_E_INVALID, "FP32 results: FP64 left contractions only");
+    return k.left_f32;
   }
-  __syncthreads();
-  if (k_begin < k_end) fetch(k_begin, 0);
-  int buf = 0;
-  for (int64_t kb = k_begin; kb < k_end; kb += BK) {
-#pragma unroll
-    for (int s = 0; s < NA; ++s) {
-      int kk, rr;
-      a_pos(tid + 256 * s, kk, rr);
-      As[kk][rr] = ra[s];
-    }
-#pragma unroll
-    for (int s = 0; s < NB; ++s) {
-      const int e = tid + 256 * s;
-      Bs[e / BJ][e % BJ] = rb[s];
-    }
-    __syncthreads();
-    // drow[buf] is free again (its step is staged): it takes the rows of step s + 2
-    if (kb + BK < k_end) fetch(kb + BK, buf ^ 1);
-    if (tid < BK) drow[buf][tid] = drm_row(kb + 2 * BK + tid);
-#pragma unroll
-    for (int s = 0; s < BK / 4; ++s) {
-      const CT a = As[4 * s + lg][16 * wave + l16];
-#pragma unroll
-      for (int cb = 0; cb < BJ / 16; ++cb) acc[cb] = P::mfma(a, Bs[4 * s + lg][16 * cb + l16], acc[cb]);
-    }
-    __syncthreads();
-    buf ^= 1;
-  }
-
-  // lane holds C[16 wave + crow(lane, v)][16 cb + l16]
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int64_t row = row0 + 16 * wave + P::crow(lane, v);
-    if (row >= rows_total) continue;
-#pragma unroll
-    for (int cb = 0; cb < BJ / 16; ++cb) {
-      const int j = j0 + 16 * cb + l16;
-      if (j >= ncols) continue;
-      const int64_t o = c * ol.cs + (row % ol.Lo) * ol.s0 + static_cast<int64_t>(j) * ol.s1 +
-                        (row / ol.Lo) * ol.s2;
-      out[o] = static_cast<TO>(acc[cb][v]);
-    }
-  }
-}
-
-// FP32 / BF16 operands take the FP32 MFMA tile, anything with FP64 the FP64 MFMA tile.
-template <bool RIGHT, typename TH, typename TD, typename TO>
-__device__ __forceinline__ void gemm_tile(const TH* __restrict__ H, int64_t L, int64_t n, int64_t Q,
-                                          const TD* __restrict__ D, int64_t sDr, int64_t sDc, int ncols,
-                                          const IndexMap& amap, const IndexMap& bmap, const HMap& hm,
-                                          int64_t kchunk, TO* __restrict__ out, const OutLayout& ol, int64_t row0,
-                                          int64_t c, int j0) {
-  if constexpr (!std::is_same_v<TH, double> && !std::is_same_v<TD, double>)
-    gemm_tile_mfma<RIGHT, TH, TD, TO, float>(H, L, n, Q, D, sDr, sDc, ncols, amap, bmap, hm, kchunk, out, ol, row0,
-                                             c, j0);
-  else
-    gemm_tile_mfma<RIGHT, TH, TD, TO, double>(H, L, n, Q, D, sDr, sDc, ncols, amap, bmap, hm, kchunk, out, ol, row0,
-                                              c, j0);
-}
-
-template <bool RIGHT, typename TH, typename TD, typename TO>
-__global__ __launch_bounds__(256) void hm_gemm(const TH* __restrict__ H, int64_t L, int64_t n, int64_t Q,
-                                               const TD* __restrict__ D, int64_t sDr, int64_t sDc,
-                                               int ncols, IndexMap amap, IndexMap bmap, HMap hm, int64_t kchunk,
-                                               TO* __restrict__ out, OutLayout ol) {
-  gemm_tile<RIGHT, TH, TD, TO>(H, L, n, Q, D, sDr, sDc, ncols, amap, bmap, hm, kchunk, out, ol,
-                               static_cast<int64_t>(blockIdx.x) * BR, blockIdx.y, blockIdx.z * BJ);
-}
-
-// Copy a descriptor from global memory into LDS (8-byte words) after locating, by
-// binary search on first_block, the task that owns this workgroup.
-template <typename Task>
-__device__ inline int64_t load_task(const Task* __restrict__ tasks, int ntasks, Task* t, int64_t b) {
-  __shared__ int idx;
-  if (threadIdx.x == 0) {
-    int lo = 0, hi = ntasks - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) / 2;
-      if (tasks[mid].first_block <= b) lo = mid;
-      else hi = mid - 1;
-    }
-    idx = lo;
-  }
-  __syncthreads();
-  static_assert(sizeof(Task) % 8 == 0, "task size");
-  const uint64_t* src = reinterpret_cast<const uint64_t*>(tasks + idx);
-  uint64_t* dst = reinterpret_cast<uint64_t*>(t);
-  for (int w = threadIdx.x; w < static_cast<int>(sizeof(Task) / 8); w += blockDim.x) dst[w] = src[w];
-  __syncthreads();
-  return b - t->first_block;
-}
-
-// Every workgroup serves one tile of one task; tasks of one launch may belong to
-// different updates (of different plans) and have different sizes.
-// Tile b of a batched contraction launch (its task found by binary search).
-template <bool RIGHT, typename TH, typename TD, typename TO>
-__device__ __forceinline__ void gemm_task_tile(const GemmTask* __restrict__ tasks, int ntasks, int64_t b) {
-  __shared__ __align__(16) char tbuf[sizeof(GemmTask)];      // raw storage: IndexMap has initialisers
-  GemmTask& t = *reinterpret_cast<GemmTask*>(tbuf);
-  int64_t rel = load_task(tasks, ntasks, &t, b);
-  const int64_t rb = rel % t.row_blocks;
-  rel /= t.row_blocks;
-  const int64_t c = rel % t.nch;
-  const int cb = static_cast<int>(rel / t.nch);
-  gemm_tile<RIGHT, TH, TD, TO>(static_cast<const TH*>(t.H), t.L, t.n, t.Q, static_cast<const TD*>(t.D), t.sDr,
-                               t.sDc, t.ncols, t.amap, t.bmap, t.hm, t.kchunk, static_cast<TO*>(t.out), t.ol,
-                               rb * BR, c, cb * BJ);
-}
-
-template <bool RIGHT, typename TH, typename TD, typename TO>
-__global__ __launch_bounds__(256) void hm_gemm_batched(const GemmTask* __restrict__ tasks, int ntasks) {
-  gemm_task_tile<RIGHT, TH, TD, TO>(tasks, ntasks, static_cast<int64_t>(blockIdx.x));
-}
-
-template <bool RIGHT, typename TH, typename TD>
-void gemm_dispatch_out(const GemmArgs& a, dim3 grid, int64_t kchunk, hipStream_t st) {
-  if (a.out_f32)
-    hipLaunchKernelGGL((hm_gemm<RIGHT, TH, TD, float>), grid, dim3(256), 0, st,
-                       static_cast<const TH*>(a.H), a.L, a.n, a.Q, static_cast<const TD*>(a.D), a.sDr,
-                       a.sDc, a.ncols, a.amap, a.bmap, a.hm, kchunk, static_cast<float*>(a.out), a.ol);
-  else
-    hipLaunchKernelGGL((hm_gemm<RIGHT, TH, TD, double>), grid, dim3(256), 0, st,
-                       static_cast<const TH*>(a.H), a.L, a.n, a.Q, static_cast<const TD*>(a.D), a.sDr,
-                       a.sDc, a.ncols, a.amap, a.bmap, a.hm, kchunk, static_cast<double*>(a.out), a.ol);
-}
-
-template <bool RIGHT, typename TH>
-void gemm_dispatch_d(const GemmArgs& a, dim3 grid, int64_t kchunk, hipStream_t st) {
-  switch (a.td) {
-    case TTNN_F64: gemm_dispatch_out<RIGHT, TH, double>(a, grid, kchunk, st); break;
-    case TTNN_F32: gemm_dispatch_out<RIGHT, TH, float>(a, grid, kchunk, st); break;
-    default: gemm_dispatch_out<RIGHT, TH, uint16_t>(a, grid, kchunk, st); break;
-  }
-}
-
-template <bool RIGHT>
-void gemm_dispatch_h(const GemmArgs& a, dim3 grid, int64_t kchunk, hipStream_t st) {
-  switch (a.th) {
-    case TTNN_F64: gemm_dispatch_d<RIGHT, double>(a, grid, kchunk, st); break;
-    case TTNN_F32: gemm_dispatch_d<RIGHT, float>(a, grid, kchunk, st); break;
-    default: gemm_dispatch_d<RIGHT, uint16_t>(a, grid, kchunk, st); break;
-  }
-}
-
-template <bool RIGHT, typename TH, typename TD>
-void batched_dispatch_d(bool out_f32, const GemmTask* tasks, int nt, int64_t blocks, hipStream_t st) {
-  if (out_f32)
-    hipLaunchKernelGGL((hm_gemm_batched<RIGHT, TH, TD, float>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
-                       st, tasks, nt);
-  else
-    hipLaunchKernelGGL((hm_gemm_batched<RIGHT, TH, TD, double>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0,
-                       st, tasks, nt);
-}
-template <bool RIGHT, typename TH>
-void batched_dispatch_h(int td, bool out_f32, const GemmTask* tasks, int nt, int64_t blocks, hipStream_t st) {
-  switch (td) {
-    case TTNN_F64: batched_dispatch_d<RIGHT, TH, double>(out_f32, tasks, nt, blocks, st); break;
-    case TTNN_F32: batched_dispatch_d<RIGHT, TH, float>(out_f32, tasks, nt, blocks, st); break;
-    default: batched_dispatch_d<RIGHT, TH, uint16_t>(out_f32, tasks, nt, blocks, st); break;
-  }
-}
-template <bool RIGHT>
-void batched_dispatch(int th, int td, bool out_f32, const GemmTask* tasks, int nt, int64_t blocks, hipStream_t st) {
-  switch (th) {
-    case TTNN_F64: batched_dispatch_h<RIGHT, double>(td, out_f32, tasks, nt, blocks, st); break;
-    case TTNN_F32: batched_dispatch_h<RIGHT, float>(td, out_f32, tasks, nt, blocks, st); break;
-    default: batched_dispatch_h<RIGHT, uint16_t>(td, out_f32, tasks, nt, blocks, st); break;
-  }
-}
-
-// part[c * stride + e] summed over c in [c0, c1) in the order of c: the loads go out
-// eight at a time with no dependence between them, the additions stay in order, so the
-// sum is bitwise that of the plain loop.
-__device__ __forceinline__ double sum_chunks(const double* __restrict__ part, int c0, int c1, int64_t stride,
-                                             int64_t e) {
-  double s = 0.0;
-  int c = c0;
-  for (; c + 8 <= c1; c += 8) {
-    double v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = part[(c + i) * stride + e];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s += v[i];
-  }
-  for (; c < c1; ++c) s += part[c * stride + e];
-  return s;
-}
-
-__device__ inline void reduce_range(const double* __restrict__ part, int nchunks, int64_t rows, int ncols, int mode,
-                                    double alpha, const IndexMap& rmap, int64_t ldr, double* __restrict__ dst,
-                                    int64_t L, int64_t kdim, int64_t start, int64_t step, int64_t stride) {
-  const int64_t total = rows * ncols;
-  for (int64_t e = start; e < total; e += step) {
-    const int64_t row = e / ncols;
-    const int j = static_cast<int>(e - row * ncols);
-    const double s = sum_chunks(part, 0, nchunks, stride, e);
-    if (mode == 0) {
-      dst[rmap(row) + ldr * j] += alpha * s;
-    } else {
-      const int64_t o = (row % L) + L * (j + kdim * (row / L));
-      if (mode == 1) dst[o] += alpha * s;
-      else dst[o] = s;
-    }
-  }
-}
-
-__device__ __forceinline__ void reduce_task_tile(const ReduceTask* __restrict__ tasks, int ntasks, int64_t b) {
-  __shared__ __align__(16) char tbuf[sizeof(ReduceTask)];
-  ReduceTask& t = *reinterpret_cast<ReduceTask*>(tbuf);
-  const int64_t rel = load_task(tasks, ntasks, &t, b);
-  reduce_range(t.part, t.nchunks, t.rows, t.ncols, t.mode, t.alpha, t.rmap, t.ldr, t.dst, t.L, t.kdim,
-               rel * 256 + threadIdx.x, t.nblocks * 256, t.cstride ? t.cstride : t.rows * t.ncols);
+  return right ? k.right : k.left;
 }
 
 __global__ __launch_bounds__(256) void reduce_batched_kernel(const ReduceTask* __restrict__ tasks, int ntasks) {
   reduce_task_tile(tasks, ntasks, static_cast<int64_t>(blockIdx.x));
 }
 
-constexpr int kFold = 32;
-
-// Fold groups of kFold consecutive chunks into each group's first slot (see
-// fold_chunks_kernel); workgroup -> (task, element block, group).
-__device__ __forceinline__ void fold_task_tile(const ReduceTask* __restrict__ tasks, int ntasks, int64_t b) {
-  __shared__ __align__(16) char tbuf[sizeof(ReduceTask)];
-  ReduceTask& t = *reinterpret_cast<ReduceTask*>(tbuf);
-  const int64_t rel = load_task(tasks, ntasks, &t, b);
-  const int64_t E = t.rows * t.ncols;
-  const int64_t eblocks = (E + 255) / 256;
-  const int64_t e = (rel % eblocks) * 256 + threadIdx.x;
-  const int g = static_cast<int>(rel / eblocks);
-  if (e >= E) return;
-  const int c0 = g * kFold, c1 = c0 + kFold < t.nchunks ? c0 + kFold : t.nchunks;
-  t.part[c0 * E + e] = sum_chunks(t.part, c0, c1, E, e);
-}
-
 __global__ __launch_bounds__(256) void fold_batched_kernel(const ReduceTask* __restrict__ tasks, int ntasks) {
   fold_task_tile(tasks, ntasks, static_cast<int64_t>(blockIdx.x));
-}
-
-// ---------------------------------------------------------------- persistent ingest
-// One launch for a whole batched round of box updates: the workgroups sweep, phase by
-// phase, every tile of every task list of the round (a level's contractions of all
-// kinds, then its chunk folds, then its reductions, level after level) and meet at a
-// grid-wide barrier between phases.  The tiles are those of the per-level launches, so
-// results are bitwise the same.  Launched cooperatively (every workgroup resident), so
-// each barrier ends; the wait is still bounded, and a wait that ran out marks the
-// round's plans (their sticky numerical status).
-struct IngestSeg {
-  int64_t tasks;        // byte offset of the task table from the program
-  int64_t blocks;
-  int32_t kind, ntasks;
-};
-struct IngestPhase {
-  IngestSeg seg[kIngestSegs];
-  int32_t nseg, pad_;
-};
-struct IngestProgram {
-  uint32_t counter;     // barrier arrivals (zero as staged)
-  int32_t nphases, nsticky, pad_;
-  int* sticky[kIngestPlans];
-  IngestPhase ph[kIngestPhases];
-};
-
-__device__ inline bool grid_barrier(uint32_t* counter, uint32_t target) {
-  __shared__ int ok;
-  __syncthreads();                                     // the workgroup's writes are done
-  if (threadIdx.x == 0) {
-    __threadfence();                                   // ... and visible device-wide
-    __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uint32_t spins = 0;
-    ok = 1;
-    while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      __builtin_amdgcn_s_sleep(2);
-      if (++spins > (1u << 24)) {                      // ~1 s: cannot happen with resident workgroups
-        ok = 0;
-        break;
-      }
-    }
-    __threadfence();                                   // later reads see the other workgroups' writes
-  }
-  __syncthreads();
-  return ok != 0;
-}
-
-template <typename TC>
-__global__ __launch_bounds__(256) void ingest_kernel(char* base) {
-  IngestProgram* prog = reinterpret_cast<IngestProgram*>(base);
-  uint32_t* counter = &prog->counter;
-  const int nph = prog->nphases;
-  for (int p = 0; p < nph; ++p) {
-    const IngestPhase& P = prog->ph[p];
-    int64_t total = 0;
-    for (int s = 0; s < P.nseg; ++s) total += P.seg[s].blocks;
-    for (int64_t b = blockIdx.x; b < total; b += gridDim.x) {
-      int s = 0;
-      int64_t rel = b;
-      while (rel >= P.seg[s].blocks) rel -= P.seg[s++].blocks;
-      const IngestSeg& g = P.seg[s];
-      const void* tasks = base + g.tasks;
-      switch (g.kind) {
-        case kSegRightRaw:
-          gemm_task_tile<true, TC, TC, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel);
-          break;
-        case kSegLeftRaw:
-          gemm_task_tile<false, TC, TC, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel);
-          break;
-        case kSegRightF64:
-          gemm_task_tile<true, double, double, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel);
-          break;
-        case kSegLeftF64:
-          gemm_task_tile<false, double, double, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel);
-          break;
-        case kSegFold:
-          fold_task_tile(static_cast<const ReduceTask*>(tasks), g.ntasks, rel);
-          break;
-        default:
-          reduce_task_tile(static_cast<const ReduceTask*>(tasks), g.ntasks, rel);
-          break;
-      }
-    }
-    if (p + 1 < nph && !grid_barrier(counter, static_cast<uint32_t>(p + 1) * gridDim.x)) {
-      if (threadIdx.x == 0)
-        for (int i = 0; i < prog->nsticky; ++i) atomicOr(prog->sticky[i], 1);
-      return;
-    }
-  }
 }
 
 __global__ void reduce_kernel(const double* __restrict__ part, int nchunks, int64_t rows, int ncols, int mode,
@@ -538,14 +142,27 @@ inline int grid_for(int64_t n) {
 
 }  // namespace
 
-int pick_chunks(int64_t rows, int ncols, int64_t K, size_t partial_cap) {
-  const int64_t row_blocks = (rows + BR - 1) / BR;
-  const int64_t col_blocks = (ncols + BJ - 1) / BJ;
-  const int64_t blocks = row_blocks * col_blocks;
-  int64_t want = 2048 / (blocks > 0 ? blocks : 1);
-  const int64_t by_len = (K + 127) / 128;              // at least ~128 terms per chunk
+// Rows per tile: a right contraction of few rows takes smaller row tiles (the spare waves
+// split each step) so that its products are not mostly padding.
+static int tile_rows(bool right, int64_t rows) { return !right || rows > 32 ? 64 : rows > 16 ? 32 : 16; }
+// Columns: at most 48 a tile (32 in the small row tiles, by registers), spread evenly over
+// the column blocks.
+static int col_blocks_of(int tr, int ncols) { return tr == 64 ? (ncols + 47) / 48 : (ncols + 31) / 32; }
+static int ncb_of(int tr, int ncols) { return ((ncols + 15) / 16 + col_blocks_of(tr, ncols) - 1) / col_blocks_of(tr, ncols); }
+static int step_of(const GemmArgs& a) {
+  const bool f64 = a.th == TTNN_F64 || a.td == TTNN_F64;
+  return (tile_rows(a.right, a.right ? a.n : a.L * a.Q) == 64 ? 8 : 16) * (f64 ? 2 : 4);
+}
+
+int pick_chunks(const GemmArgs& a, size_t partial_cap) {
+  const int64_t rows = a.right ? a.n : a.L * a.Q, K = a.right ? a.L * a.Q : a.n;
+  if (rows <= 0 || a.ncols <= 0) return 1;
+  const int tr = tile_rows(a.right, rows);
+  const int64_t blocks = (rows + tr - 1) / tr * col_blocks_of(tr, a.ncols);
+  int64_t want = kTargetBlocks / blocks;
+  const int64_t by_len = (K + kMinSteps * step_of(a) - 1) / (kMinSteps * step_of(a));
   if (want > by_len) want = by_len;
-  const int64_t cap = static_cast<int64_t>(partial_cap / static_cast<size_t>(rows * ncols));
+  const int64_t cap = static_cast<int64_t>(partial_cap / static_cast<size_t>(rows * a.ncols));
   if (want > cap) want = cap;
   if (want > 65535) want = 65535;
   return static_cast<int>(want < 1 ? 1 : want);
@@ -555,24 +172,49 @@ int gemm_chunks(const GemmArgs& a, int64_t* kchunk_out) {
   const int64_t rows = a.right ? a.n : a.L * a.Q;
   const int64_t K = a.right ? a.L * a.Q : a.n;
   if (rows <= 0 || a.ncols <= 0) return 0;
+  const int64_t bk = step_of(a);
   int64_t kchunk = (K + a.nchunks - 1) / a.nchunks;
-  kchunk = ((kchunk + BK - 1) / BK) * BK;
-  if (kchunk < BK) kchunk = BK;
+  kchunk = ((kchunk + bk - 1) / bk) * bk;
+  if (kchunk < bk) kchunk = bk;
   const int nch = static_cast<int>((K + kchunk - 1) / kchunk);
   if (kchunk_out) *kchunk_out = kchunk;
   return nch > 0 ? nch : 1;
 }
 
-int launch_gemm(const GemmArgs& a, hipStream_t st) {
-  int64_t kchunk = 0;
-  const int nch = gemm_chunks(a, &kchunk);
-  if (nch == 0) return 0;
+static bool fill_task(const GemmArgs& a, GemmTask& t, size_t& lds) {
+  const int nch = gemm_chunks(a, &t.kchunk);
+  if (nch == 0) return false;
   const int64_t rows = a.right ? a.n : a.L * a.Q;
-  dim3 grid(static_cast<unsigned>((rows + BR - 1) / BR), static_cast<unsigned>(nch),
-            static_cast<unsigned>((a.ncols + BJ - 1) / BJ));
-  if (a.right) gemm_dispatch_h<true>(a, grid, kchunk, st);
-  else gemm_dispatch_h<false>(a, grid, kchunk, st);
-  return nch;
+  t.H = a.H;
+  t.D = a.D;
+  t.out = a.out;
+  t.L = a.L;
+  t.n = a.n;
+  t.Q = a.Q;
+  t.sDr = a.sDr;
+  t.sDc = a.sDc;
+  t.ncols = a.ncols;
+  t.amap = a.amap;
+  t.bmap = a.bmap;
+  t.hm = a.hm;
+  t.ol = a.ol;
+  t.tr = tile_rows(a.right, rows);
+  t.ncb = ncb_of(t.tr, a.ncols);
+  t.row_blocks = (rows + t.tr - 1) / t.tr;
+  t.nch = nch;
+  t.col_blocks = col_blocks_of(t.tr, a.ncols);
+  lds = std::max(lds, tile_lds(t.tr, t.ncb));
+  return true;
+}
+
+int launch_gemm(const GemmArgs& a, hipStream_t st) {
+  GemmTask t{};
+  size_t lds = 0;
+  if (!fill_task(a, t, lds)) return 0;
+  const int64_t blocks = t.row_blocks * t.nch * t.col_blocks;
+  TTNN_REQUIRE(blocks < (int64_t(1) << 31), TTNN_E_INVALID, "contraction launch too large");
+  tiles_for(a.right, a.th, a.td, a.out_f32)(nullptr, 0, t, blocks, lds, st);
+  return static_cast<int>(t.nch);
 }
 
 BatchedGemm plan_gemm_batched(const std::vector<GemmArgs>& args) {
@@ -587,25 +229,7 @@ BatchedGemm plan_gemm_batched(const std::vector<GemmArgs>& args) {
     TTNN_REQUIRE(a.right == b.right && a.th == b.th && a.td == b.td && a.out_f32 == b.out_f32, TTNN_E_INVALID,
                  "batched contraction with mixed kinds");
     GemmTask t{};
-    const int nch = gemm_chunks(a, &t.kchunk);
-    if (nch == 0) continue;
-    const int64_t rows = a.right ? a.n : a.L * a.Q;
-    t.H = a.H;
-    t.D = a.D;
-    t.out = a.out;
-    t.L = a.L;
-    t.n = a.n;
-    t.Q = a.Q;
-    t.sDr = a.sDr;
-    t.sDc = a.sDc;
-    t.ncols = a.ncols;
-    t.amap = a.amap;
-    t.bmap = a.bmap;
-    t.hm = a.hm;
-    t.ol = a.ol;
-    t.row_blocks = (rows + BR - 1) / BR;
-    t.nch = nch;
-    t.col_blocks = (a.ncols + BJ - 1) / BJ;
+    if (!fill_task(a, t, b.lds)) continue;
     t.first_block = b.blocks;
     b.blocks += t.row_blocks * t.nch * t.col_blocks;
     b.tasks.push_back(t);
@@ -617,8 +241,7 @@ BatchedGemm plan_gemm_batched(const std::vector<GemmArgs>& args) {
 void launch_gemm_staged(const BatchedGemm& b, const GemmTask* d, hipStream_t st) {
   if (b.tasks.empty()) return;
   const int nt = static_cast<int>(b.tasks.size());
-  if (b.right) batched_dispatch<true>(b.th, b.td, b.out_f32, d, nt, b.blocks, st);
-  else batched_dispatch<false>(b.th, b.td, b.out_f32, d, nt, b.blocks, st);
+  tiles_for(b.right, b.th, b.td, b.out_f32)(d, nt, GemmTask{}, b.blocks, b.lds, st);
 }
 
 void launch_gemm_batched(const std::vector<GemmArgs>& args, hipStream_t st) {
@@ -731,21 +354,19 @@ void launch_finite_check(const double* p, int64_t n, int* flag, hipStream_t st) 
 
 // ---------------------------------------------------------------- persistent ingest (host)
 namespace {
-template <typename TC>
-int ingest_grid(int64_t want) {
+int ingest_grid(const void* kernel, int64_t want, size_t lds) {
   static std::mutex mu;
-  static std::map<int, int> slots;              // device -> resident workgroups of the kernel
+  static std::map<std::tuple<int, const void*, size_t>, int> slots;   // resident workgroups by device, kernel and LDS
   int dev = 0;
   TTNN_HIP(hipGetDevice(&dev));
   std::lock_guard<std::mutex> lock(mu);
-  auto it = slots.find(dev);
+  auto it = slots.find({dev, kernel, lds});
   if (it == slots.end()) {
     int coop = 0, cus = 0, per = 0;
     TTNN_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
     TTNN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    TTNN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(ingest_kernel<TC>),
-                                                            256, 0));
-    it = slots.emplace(dev, coop ? per * cus : 0).first;
+    TTNN_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, 256, lds));
+    it = slots.emplace(std::make_tuple(dev, kernel, lds), coop ? per * cus : 0).first;
   }
   if (it->second <= 0) return 0;
   return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(want, it->second)));
@@ -767,12 +388,13 @@ bool launch_ingest(int cd, const std::vector<BatchedGemm>& gl, const std::vector
     return static_cast<int64_t>(at);
   };
   int64_t most = 0;
-  size_t g0 = 0;
+  size_t g0 = 0, lds = 0;
   for (size_t lv = 0; lv < rl.size(); ++lv) {
     IngestPhase ph{};
     for (size_t k = g0; k < level_end[lv]; ++k) {
       const BatchedGemm& b = gl[k];
       if (b.tasks.empty()) continue;
+      lds = std::max(lds, b.lds);
       if (b.out_f32 || ph.nseg == kIngestSegs) return false;
       int kind;
       if (b.th == cd && b.td == cd) kind = b.right ? kSegRightRaw : kSegLeftRaw;
@@ -811,9 +433,8 @@ bool launch_ingest(int cd, const std::vector<BatchedGemm>& gl, const std::vector
   }
   if (phases.empty()) return true;
   if (phases.size() > static_cast<size_t>(kIngestPhases)) return false;
-  const int grid = cd == TTNN_BF16 ? ingest_grid<uint16_t>(most)
-                   : cd == TTNN_F32 ? ingest_grid<float>(most)
-                                    : ingest_grid<double>(most);
+  const void* kernel = (cd == TTNN_BF16 ? tile_kernels_bf16() : cd == TTNN_F32 ? tile_kernels_f32() : tile_kernels_f64()).ingest;
+  const int grid = ingest_grid(kernel, most, lds);
   if (grid <= 0) return false;
   std::vector<char> host(off, 0);
   IngestProgram* prog = reinterpret_cast<IngestProgram*>(host.data());
@@ -830,16 +451,7 @@ bool launch_ingest(int cd, const std::vector<BatchedGemm>& gl, const std::vector
   StagingLock lock;
   char* d = static_cast<char*>(stage_descriptors(host.data(), host.size(), st));
   void* args[] = {&d};
-  hipError_t e;
-  if (cd == TTNN_BF16)
-    e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(ingest_kernel<uint16_t>), dim3(grid), dim3(256),
-                                   args, 0, st);
-  else if (cd == TTNN_F32)
-    e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(ingest_kernel<float>), dim3(grid), dim3(256), args,
-                                   0, st);
-  else
-    e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(ingest_kernel<double>), dim3(grid), dim3(256),
-                                   args, 0, st);
+  const hipError_t e = hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(256), args, lds, st);
   TTNN_HIP(e);
   fence_descriptors(st);
   return true;

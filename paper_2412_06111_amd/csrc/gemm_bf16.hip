@@ -1,0 +1,11 @@
+// The generic contraction with BF16 operands (gemm_tile.hpp).
+#include "gemm_tile.hpp"
+
+namespace ttnn {
+
+TileKernels tile_kernels_bf16() {
+  return TileKernels{launch_tiles<true, uint16_t, double>, launch_tiles<false, uint16_t, double>, nullptr,
+                     reinterpret_cast<const void*>(ingest_kernel<uint16_t>)};
+}
+
+}  // namespace ttnn

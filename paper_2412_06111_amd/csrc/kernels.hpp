@@ -56,8 +56,9 @@ struct GemmArgs {
 // Returns the number of chunks actually written (<= a.nchunks); 0 if nothing to do.
 int launch_gemm(const GemmArgs& a, hipStream_t stream);
 
-// choose the split over the contraction index; returns the number of chunks
-int pick_chunks(int64_t rows, int ncols, int64_t K, size_t partial_cap);
+// choose the split of `a` over its contraction index (a.nchunks is not read); returns the
+// number of chunks
+int pick_chunks(const GemmArgs& a, size_t partial_cap);
 // The number of chunks launch_gemm writes for `a` (0 if nothing to do) and their length.
 int gemm_chunks(const GemmArgs& a, int64_t* kchunk);
 
@@ -72,7 +73,7 @@ struct GemmTask {
   IndexMap amap, bmap;
   HMap hm;
   OutLayout ol;
-  int32_t ncols, pad_;
+  int32_t ncols, tr, ncb, pad_;            // tr x 16 ncb: the tile
 };
 struct ReduceTask {
   double* part = nullptr;
@@ -96,6 +97,7 @@ void launch_reduce_batched(const std::vector<ReduceTask>& tasks, hipStream_t str
 struct BatchedGemm {
   std::vector<GemmTask> tasks;
   int64_t blocks = 0;
+  size_t lds = 0;                          // dynamic LDS of the largest tile
   bool right = true, out_f32 = false;
   int th = TTNN_F64, td = TTNN_F64;
 };

@@ -1,0 +1,59 @@
+"""Edges of the generic contraction's tile: row tiles of 16, 32 and 64 with remainders,
+one to three column blocks and a second column tile, contractions of one value, of one
+step more or less than a whole one, and past one offset table; rows along memory (node
+1), contraction along memory (node 2) and the left form (root), packed and in place."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from gpu_util import TOL_ARITH, failures, sketch_errors, to_device
+
+pytestmark = pytest.mark.gpu
+
+# (extent 1, extent 2, r, p)
+SHAPES = [(1, 1, 1, 0), (15, 33, 3, 1), (16, 31, 16, 1), (17, 64, 17, 15), (32, 257, 15, 1), (33, 255, 32, 1),
+          (64, 513, 31, 17), (65, 32, 33, 15), (40, 1030, 48, 1), (130, 70, 49, 48)]
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("e1,e2,r,p", SHAPES)
+def test_tile_edges(e1, e2, r, p, dtype):
+    import paper_2412_06111_amd as P
+    spec, dims, off = (1, 2), (e1 + 3, e2 + 2), (2, 1)
+    g = np.random.default_rng(7 * e1 + e2)
+    full = np.zeros(dims)
+    full[2:2 + e1, 1:1 + e2] = g.standard_normal((e1, e2))
+    dev, consumed = to_device(full, dtype)
+    view = dev.view(dims[1], dims[0])[1:1 + e2, 2:2 + e1]
+    tree = O.Tree(spec, dims, r, p)
+    sk = O.sketch(consumed, tree, O.DRMs(tree, 5, "ttnn", dtype), "ttnn")
+    for block in (view, view.contiguous().reshape(-1)):
+        plan = P.Plan(spec, dims, r, p, variant="ttnn", dtype=dtype, seed=5)
+        plan.update(block, extent=(e1, e2), offset=off)
+        torch.cuda.synchronize()
+        errs = sketch_errors(plan, tree, sk)
+        assert not failures(errs, TOL_ARITH[dtype]), errs
+        plan.close()
+
+
+def test_tile_ignores_values_past_the_box():
+    """Rows, columns and contraction values past the end are masked: infinities and NaN
+    around a box read in place do not reach its sketch."""
+    import paper_2412_06111_amd as P
+    spec, dims, ext, off = ((1, 2), 3), (21, 19, 23), (17, 13, 9), (2, 3, 5)
+    g = np.random.default_rng(3)
+    box = g.standard_normal(ext)
+    t = torch.full(tuple(reversed(dims)), float("nan"), dtype=torch.float32, device="cuda")
+    t[::2] = float("inf")
+    at = tuple(slice(o, o + e) for o, e in zip(reversed(off), reversed(ext)))
+    t[at] = torch.from_numpy(np.ascontiguousarray(box.T)).float().cuda()
+    full = np.zeros(dims)
+    full[tuple(slice(o, o + e) for o, e in zip(off, ext))] = t[at].double().cpu().numpy().T
+    tree = O.Tree(spec, dims, 5, 3)
+    sk = O.sketch(full, tree, O.DRMs(tree, 9, "ttnn", "f32"), "ttnn")
+    plan = P.Plan(spec, dims, 5, 3, variant="ttnn", dtype="f32", seed=9)
+    plan.update(t[at], extent=ext, offset=off)
+    torch.cuda.synchronize()
+    errs = sketch_errors(plan, tree, sk)
+    assert not failures(errs, TOL_ARITH["f32"]), errs
