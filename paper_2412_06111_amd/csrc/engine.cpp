@@ -1065,12 +1065,19 @@ void update_rank1(Plan& P, int nterms, const double* const* factors, const doubl
       }
       return goff[s];
     };
-    double* w = P.r1 + static_cast<int64_t>(kRank1Batch) * P.r1_w;     // m x rmax
-    const int64_t wstride = P.r1_rmax;
+    // X_t^T v_t of every node (m x r_t each), then all outer products in one launch
+    double* w = P.r1 + static_cast<int64_t>(kRank1Batch) * P.r1_w;
+    OuterList ol;
+    ol.m = m;
+    ol.d = d;
+    ol.f = f;
+    ol.len = P.dims;
+    ol.alpha = alphas + t0;
+    ol.gstride = static_cast<int64_t>(P.r1_w);
     for (size_t v = 1; v < P.nodes.size(); ++v) {
       const Node& t = P.nodes[v];
       if (t.ident) continue;                    // a free mode: no sketch of its own
-      KronBatch kx, ku;
+      KronBatch kx;
       for (int y = 0; y < m; ++y) {
         KronVec k;
         if (P.variant == TTNN_STTNN) {
@@ -1089,20 +1096,16 @@ void update_rank1(Plan& P, int nterms, const double* const* factors, const doubl
             if (mu < t.first || mu > t.last) k.push(f[y * d + mu], P.dims[mu]);
         }
         kx.push(k);
-        ku.push(modes(y, t.first, t.last), alphas[t0 + y]);
       }
       const bool raw = t.S.empty();
       launch_kron_gemv(raw ? t.Xc : static_cast<const void*>(t.X64), raw ? cd : TTNN_F64, t.m, t.r, kx, P.partial,
-                       P.partial_elems, w, wstride, P.rank1_form == TTNN_R1_GROUPED, st);
-      launch_outer_acc(t.R, t.n, t.r, ku, w, wstride, st);
+                       P.partial_elems, w, t.r, P.rank1_form == TTNN_R1_GROUPED, st);
+      ol.nodes.push_back(OuterNode{t.R, w, t.n, t.r, t.first, t.last - t.first + 1});
+      w += static_cast<int64_t>(kRank1Batch) * t.r;
     }
-    KronBatch kg;
-    for (int y = 0; y < m; ++y) {
-      KronVec k;
-      for (int c : P.nodes[0].children) k.push(P.r1 + y * P.r1_w + g_of(c), P.nodes[c].k);
-      kg.push(k, alphas[t0 + y]);
-    }
-    launch_outer_acc(P.psi_root, P.psi_root_len, 1, kg, nullptr, 0, st);
+    for (int c : P.nodes[0].children) ol.root.push(P.r1 + g_of(c), P.nodes[c].k);
+    ol.nodes.push_back(OuterNode{P.psi_root, nullptr, P.psi_root_len, 1, -1, ol.root.n});
+    launch_outer_list(ol, st);
   }
 }
 

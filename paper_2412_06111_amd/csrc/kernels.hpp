@@ -218,11 +218,26 @@ struct KronBatch {
 // caller keeps one choice for all of a plan's terms).
 void launch_kron_gemv(const void* D, int dt, int64_t rows, int ncols, const KronBatch& kb, double* partial,
                       size_t partial_elems, double* w, int64_t wstride, bool grouped, hipStream_t stream);
-// R[i + n j] += alpha_y * ku_y(i) * (w ? w[y * wstride + j] : 1) for y = 0 .. m-1 in that
-// order, R column-major n x ncols (each entry sees the terms' additions in order, as
-// with one launch per term).
-void launch_outer_acc(double* R, int64_t n, int ncols, const KronBatch& ku, const double* w, int64_t wstride,
-                      hipStream_t stream);
+// For every node of the list, R[i + n j] += alpha_y * u_y(i) * (w ? w[y * ncols + j] : 1)
+// for the terms y = 0 .. m-1 in that order, R column-major n x ncols and u_y the Kronecker
+// vector of the term's factors first .. first + cnt - 1 (first < 0: the root's factors,
+// term y's gstride after term 0's); one launch for up to 24 nodes.
+struct OuterNode {
+  double* R;
+  const double* w;
+  int64_t n;
+  int ncols, first, cnt;
+};
+struct OuterList {
+  std::vector<OuterNode> nodes;
+  int m = 0, d = 0;
+  const double* const* f = nullptr;        // term y's factor of mode mu: f[y d + mu]
+  const int64_t* len = nullptr;            // of the modes
+  const double* alpha = nullptr;
+  KronVec root;                            // term 0's
+  int64_t gstride = 0;
+};
+void launch_outer_list(const OuterList& o, hipStream_t stream);
 
 // ---------------------------------------------------------------- whole-tensor right sketch on MFMA
 // H (dtype dt) viewed as [L][n][Q] (l fastest); Xt is the transposed DRM copy (r x m,

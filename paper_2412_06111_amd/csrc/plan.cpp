@@ -403,15 +403,14 @@ std::unique_ptr<Plan> build_plan(const ttnn_problem* pr, hipStream_t stream, boo
   P->partial = static_cast<double*>(P->alloc(sizeof(double) * P->partial_elems));
   P->work = static_cast<double*>(P->alloc(sizeof(double) * P->work_elems));
   {
-    size_t ks = 0, rmax = 1;
+    size_t ks = 0, rsum = 0;
     for (size_t v = 1; v < P->nodes.size(); ++v) {       // g_s of every group, free modes too
       ks += static_cast<size_t>(P->nodes[v].k);
-      if (!P->nodes[v].ident) rmax = std::max(rmax, static_cast<size_t>(P->nodes[v].r));
+      if (!P->nodes[v].ident) rsum += static_cast<size_t>(P->nodes[v].r);
     }
-    // per term of a rank-1 batch: the g_s (ks) and one node's X_t^T v (rmax)
+    // per term of a rank-1 batch: the g_s (ks) and every node's X_t^T v_t (rsum)
     P->r1_w = ks;
-    P->r1_rmax = rmax;
-    P->r1 = static_cast<double*>(P->alloc(sizeof(double) * kRank1Batch * (ks + rmax)));
+    P->r1 = static_cast<double*>(P->alloc(sizeof(double) * kRank1Batch * (ks + rsum)));
   }
 
   // TTNN_DISABLE_FUSED=1 routes every update through the generic kernels (parity checks)

@@ -87,9 +87,8 @@ struct Plan {
   double* partial = nullptr;               // split-K partials
   size_t partial_elems = 0;
   double* r1 = nullptr;                    // rank-1 updates: per batch term the g_s vectors
-                                           // (r1_w each), then per term one X_t^T v (r1_rmax)
+                                           // (r1_w each), then per node and term X_t^T v_t
   size_t r1_w = 0;                         // g_s entries of a term (sum of k_s)
-  size_t r1_rmax = 1;                      // largest r_t
   double* work = nullptr;                  // assembly / reconstruction scratch
   size_t work_elems = 0;
   int* d_flag = nullptr;                   // numeric-status flag written by kernels

@@ -122,3 +122,48 @@ def test_rank1_mfma_form(P, name, variant, dtype, m):
     assert not bad, bad
     one.close()
     many.close()
+
+
+# edges of the grouped form: two i1 sharing column blocks (r <= 8, 17 .. 24) with odd e1,
+# one i1 a time with one to four column blocks, e0 no multiple of 4, e0 up to 32 and past
+# it, i1 ranges split over workgroups, and (the last) several blocks a workgroup
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("dims,r", [((16, 4, 5), 5), ((17, 5, 31), 12), ((33, 63, 18), 20), ((64, 19, 16), 24),
+                                    ((32, 64, 37), 40), ((35, 22, 17), 50), ((16, 5, 64, 64, 3), 7)])
+def test_rank1_mfma_edges(P, dims, r, dtype):
+    spec, p, m = tuple(range(1, len(dims) + 1)), 1, 5
+    g = np.random.default_rng(sum(dims))
+    vecs = [[g.standard_normal(n) for n in dims] for _ in range(m)]
+    alphas = [float(a) for a in g.uniform(-2, 2, size=m)]
+    dev = [[torch.from_numpy(v).cuda() for v in term] for term in vecs]
+    one = P.Plan(spec, dims, r, p, variant="ttnn", dtype=dtype, seed=8)
+    many = P.Plan(spec, dims, r, p, variant="ttnn", dtype=dtype, seed=8)
+    one.set_rank1_form("grouped")
+    many.set_rank1_form("grouped")
+    for term, a in zip(dev, alphas):
+        one.update_rank1(term, alpha=a)
+    many.update_rank1_batched(dev, alphas)
+    torch.cuda.synchronize()
+    tree = O.Tree(spec, dims, r, p)
+    T = np.zeros(dims)
+    for term, a in zip(vecs, alphas):
+        outer = term[0]
+        for v in term[1:]:
+            outer = np.multiply.outer(outer, v)
+        T += a * outer
+    D = O.DRMs(tree, 8, "ttnn", dtype)
+    for n in tree.nodes[1:]:
+        cid = many.node(n.modes)
+        a, b = (plan.read_sketch(cid, P.SK_R).cpu().numpy() for plan in (one, many))
+        assert np.array_equal(a.view(np.uint64), b.view(np.uint64))
+        want = _unfold(T, n) @ D.X[n.id]
+        assert np.linalg.norm(b - want) <= 1e-10 * np.linalg.norm(want), n.modes
+    one.close()
+    many.close()
+
+
+def _unfold(T, n):
+    inside = [m - 1 for m in n.modes]
+    rest = [a for a in range(T.ndim) if a not in inside]
+    rows = int(np.prod([T.shape[a] for a in inside]))
+    return np.transpose(T, inside + rest).reshape((rows, -1), order="F")
