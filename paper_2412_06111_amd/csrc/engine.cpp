@@ -74,13 +74,11 @@ void left_op(Plan& P, GemmArgs g, double* dst, int mode, double alpha, hipStream
   g.nchunks = pick_chunks(g, P.partial_elems);
   if (g.nchunks == 1 && mode == 2) {
     g.out = dst;
-    g.out_f32 = false;
     g.ol = OutLayout{g.L, 1, g.L, g.L * g.ncols, 0};
     launch_gemm(g, st);
     return;
   }
   g.out = P.partial;
-  g.out_f32 = false;
   g.ol = OutLayout{INT64_MAX, g.ncols, 1, 0, rows * g.ncols};
   const int nch = launch_gemm(g, st);
   if (nch == 0) return;
@@ -330,7 +328,6 @@ void record_box(Plan& P, const void* block, const int64_t* off, const int64_t* e
     g.right = false;
     const int64_t rows = g.L * g.Q;
     g.nchunks = pick_chunks(g, P.partial_elems);
-    g.out_f32 = false;
     BoxOp op;
     if (g.nchunks == 1 && mode == 2) {
       g.out = dst;
@@ -506,7 +503,7 @@ void run_box_ops_batched(const std::vector<Plan*>& plans, const std::vector<cons
       std::vector<GemmArgs> kind;
       for (size_t b = a; b < gemms.size(); ++b) {
         const GemmArgs &x = gemms[a], &y = gemms[b];
-        if (taken[b] || x.right != y.right || x.th != y.th || x.td != y.td || x.out_f32 != y.out_f32) continue;
+        if (taken[b] || x.right != y.right || x.th != y.th || x.td != y.td) continue;
         kind.push_back(y);
         taken[b] = true;
       }
@@ -978,34 +975,10 @@ void run_reconstruct(Plan& P, const double* const* cores, void* out, int out_dty
         const bool last = i + 1 == m;
         if (last && v == 0) {
           batch.flush();
-          // final step writes the dense tensor (dtype of the caller's buffer) directly
-          GemmArgs g;
-          g.right = false;
-          g.H = cur;
-          g.th = TTNN_F64;
-          g.L = 1;
-          for (size_t j = 0; j < i; ++j) g.L *= sizes[j];
-          g.n = sizes[i];
-          g.Q = 1;
-          g.D = U[t.children[i]];
-          g.td = TTNN_F64;
-          g.sDr = c.n;
-          g.sDc = 1;
-          g.ncols = static_cast<int>(c.n);
-          IndexMap id;
-          id.push(g.n, 0, 1);
-          g.amap = id;
-          g.nchunks = 1;
-          g.out = out;
-          g.out_f32 = out_dtype == TTNN_F32;
-          g.ol = OutLayout{g.L, 1, g.L, g.L * g.ncols, 0};
-          if (out_dtype == TTNN_F64) {
-            std::vector<GJob> one{mode_job(cur, sizes, static_cast<int>(i), U[t.children[i]], c.n, 1, c.n,
-                                           static_cast<double*>(out))};
-            launch_bgemm64(one, P.g64_part, P.g64_part_elems, st);
-          } else {
-            launch_gemm(g, st);
-          }
+          // the final step writes the dense tensor in the type of the caller's buffer
+          int64_t L = 1;
+          for (size_t j = 0; j < i; ++j) L *= sizes[j];
+          launch_outer64(cur, U[t.children[i]], L, c.n, static_cast<int>(sizes[i]), out, out_dtype == TTNN_F32, st);
           break;
         }
         double* o = last ? dest : bufs[i % 2];

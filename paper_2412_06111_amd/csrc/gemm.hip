@@ -26,14 +26,10 @@ constexpr int kMinSteps = 8;          // and the least steps a chunk is worth (b
                                       // descriptor, tables and first loads outweigh its steps)
 
 // The kernels of a contraction's operand types: the raw block with the compute-type maps,
-// or an FP64 intermediate with the FP64 maps; FP32 results only from the reconstruction.
-LaunchTiles tiles_for(bool right, int th, int td, bool out_f32) {
+// or an FP64 intermediate with the FP64 maps.
+LaunchTiles tiles_for(bool right, int th, int td) {
   TTNN_REQUIRE(th == td, TTNN_E_INVALID, "contraction operands of different types");
   const TileKernels k = th == TTNN_F64 ? tile_kernels_f64() : th == TTNN_F32 ? tile_kernels_f32() : tile_kernels_bf16();
-  if (out_f32) {
-    TTNN_REQUIRE(!right && k.left_f32, TTNN_E_INVALID, "FP32 results: FP64 left contractions only");
-    return k.left_f32;
-  }
   return right ? k.right : k.left;
 }
 
@@ -213,7 +209,7 @@ int launch_gemm(const GemmArgs& a, hipStream_t st) {
   if (!fill_task(a, t, lds)) return 0;
   const int64_t blocks = t.row_blocks * t.nch * t.col_blocks;
   TTNN_REQUIRE(blocks < (int64_t(1) << 31), TTNN_E_INVALID, "contraction launch too large");
-  tiles_for(a.right, a.th, a.td, a.out_f32)(nullptr, 0, t, blocks, lds, st);
+  tiles_for(a.right, a.th, a.td)(nullptr, 0, t, blocks, lds, st);
   return static_cast<int>(t.nch);
 }
 
@@ -223,10 +219,9 @@ BatchedGemm plan_gemm_batched(const std::vector<GemmArgs>& args) {
   b.right = args[0].right;
   b.th = args[0].th;
   b.td = args[0].td;
-  b.out_f32 = args[0].out_f32;
   b.tasks.reserve(args.size());
   for (const GemmArgs& a : args) {
-    TTNN_REQUIRE(a.right == b.right && a.th == b.th && a.td == b.td && a.out_f32 == b.out_f32, TTNN_E_INVALID,
+    TTNN_REQUIRE(a.right == b.right && a.th == b.th && a.td == b.td, TTNN_E_INVALID,
                  "batched contraction with mixed kinds");
     GemmTask t{};
     if (!fill_task(a, t, b.lds)) continue;
@@ -241,7 +236,7 @@ BatchedGemm plan_gemm_batched(const std::vector<GemmArgs>& args) {
 void launch_gemm_staged(const BatchedGemm& b, const GemmTask* d, hipStream_t st) {
   if (b.tasks.empty()) return;
   const int nt = static_cast<int>(b.tasks.size());
-  tiles_for(b.right, b.th, b.td, b.out_f32)(d, nt, GemmTask{}, b.blocks, b.lds, st);
+  tiles_for(b.right, b.th, b.td)(d, nt, GemmTask{}, b.blocks, b.lds, st);
 }
 
 void launch_gemm_batched(const std::vector<GemmArgs>& args, hipStream_t st) {
@@ -395,7 +390,7 @@ bool launch_ingest(int cd, const std::vector<BatchedGemm>& gl, const std::vector
       const BatchedGemm& b = gl[k];
       if (b.tasks.empty()) continue;
       lds = std::max(lds, b.lds);
-      if (b.out_f32 || ph.nseg == kIngestSegs) return false;
+      if (ph.nseg == kIngestSegs) return false;
       int kind;
       if (b.th == cd && b.td == cd) kind = b.right ? kSegRightRaw : kSegLeftRaw;
       else if (b.th == TTNN_F64 && b.td == TTNN_F64) kind = b.right ? kSegRightF64 : kSegLeftF64;

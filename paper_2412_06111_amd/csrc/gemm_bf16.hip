@@ -4,7 +4,7 @@
 namespace ttnn {
 
 TileKernels tile_kernels_bf16() {
-  return TileKernels{launch_tiles<true, uint16_t, double>, launch_tiles<false, uint16_t, double>, nullptr,
+  return TileKernels{launch_tiles<true, uint16_t>, launch_tiles<false, uint16_t>,
                      reinterpret_cast<const void*>(ingest_kernel<uint16_t>)};
 }
 

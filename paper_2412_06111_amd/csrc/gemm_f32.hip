@@ -4,7 +4,7 @@
 namespace ttnn {
 
 TileKernels tile_kernels_f32() {
-  return TileKernels{launch_tiles<true, float, double>, launch_tiles<false, float, double>, nullptr,
+  return TileKernels{launch_tiles<true, float>, launch_tiles<false, float>,
                      reinterpret_cast<const void*>(ingest_kernel<float>)};
 }
 

@@ -4,7 +4,7 @@
 namespace ttnn {
 
 TileKernels tile_kernels_f64() {
-  return TileKernels{launch_tiles<true, double, double>, launch_tiles<false, double, double>, launch_tiles<false, double, float>,
+  return TileKernels{launch_tiles<true, double>, launch_tiles<false, double>,
                      reinterpret_cast<const void*>(ingest_kernel<double>)};
 }
 

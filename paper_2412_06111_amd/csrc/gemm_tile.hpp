@@ -85,7 +85,7 @@ template <typename CT> __device__ inline CT to_ct(float v) { return static_cast<
 template <typename CT> __device__ inline CT to_ct(double v) { return static_cast<CT>(v); }
 template <typename CT> __device__ inline CT to_ct(uint16_t v) { return static_cast<CT>(bf16_bits_to_f32(v)); }
 
-template <bool RIGHT, typename TH, typename TD, typename TO, int TR, int NCB>
+template <bool RIGHT, typename TH, typename TD, int TR, int NCB>
 __device__ __forceinline__ void gemm_tile(const GemmTask& t, int64_t row0, int64_t c, int j0, char* lds) {
   using CT = std::conditional_t<std::is_same_v<TH, double> || std::is_same_v<TD, double>, double, float>;
   using P = Pol<std::is_same_v<CT, double> ? TTNN_F64 : TTNN_F32>;
@@ -293,7 +293,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTask& t, int64_t row0, int64
   }
 
   // lane holds C[16 wr + crow(lane, v)][16 cb + l16]
-  TO* __restrict__ out = static_cast<TO*>(t.out) + c * t.ol.cs;
+  double* __restrict__ out = static_cast<double*>(t.out) + c * t.ol.cs;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int64_t row = row0 + 16 * wr + P::crow(lane, v);
@@ -303,29 +303,29 @@ __device__ __forceinline__ void gemm_tile(const GemmTask& t, int64_t row0, int64
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
       const int j = j0 + 16 * cb + l16;
-      if (j < ncols) out[lo * t.ol.s0 + static_cast<int64_t>(j) * t.ol.s1 + hi * t.ol.s2] = static_cast<TO>(sum[cb][v]);
+      if (j < ncols) out[lo * t.ol.s0 + static_cast<int64_t>(j) * t.ol.s1 + hi * t.ol.s2] = sum[cb][v];
     }
   }
 }
 
 // Tile rel of a task, in the task's form (rows per tile and column blocks).
-template <bool RIGHT, typename TH, typename TD, typename TO, int TR>
+template <bool RIGHT, typename TH, typename TD, int TR>
 __device__ __forceinline__ void gemm_form(const GemmTask& t, int64_t rb, int64_t c, int cb, char* lds) {
   const int ncb = t.ncb, j0 = cb * 16 * ncb;
-  if (ncb == 1) gemm_tile<RIGHT, TH, TD, TO, TR, 1>(t, rb * TR, c, j0, lds);
-  else if (ncb == 2) gemm_tile<RIGHT, TH, TD, TO, TR, 2>(t, rb * TR, c, j0, lds);
-  else if constexpr (TR == 64) gemm_tile<RIGHT, TH, TD, TO, TR, 3>(t, rb * TR, c, j0, lds);
+  if (ncb == 1) gemm_tile<RIGHT, TH, TD, TR, 1>(t, rb * TR, c, j0, lds);
+  else if (ncb == 2) gemm_tile<RIGHT, TH, TD, TR, 2>(t, rb * TR, c, j0, lds);
+  else if constexpr (TR == 64) gemm_tile<RIGHT, TH, TD, TR, 3>(t, rb * TR, c, j0, lds);
 }
-template <bool RIGHT, typename TH, typename TD, typename TO>
+template <bool RIGHT, typename TH, typename TD>
 __device__ __forceinline__ void gemm_any(const GemmTask& t, int64_t rel, char* lds) {
   int64_t rb, c, cb;
   split_at(rel, t.row_blocks, rb, rel);
   split_at(rel, t.nch, c, cb);
   if constexpr (RIGHT) {
-    if (t.tr == 16) return gemm_form<RIGHT, TH, TD, TO, 16>(t, rb, c, static_cast<int>(cb), lds);
-    if (t.tr == 32) return gemm_form<RIGHT, TH, TD, TO, 32>(t, rb, c, static_cast<int>(cb), lds);
+    if (t.tr == 16) return gemm_form<RIGHT, TH, TD, 16>(t, rb, c, static_cast<int>(cb), lds);
+    if (t.tr == 32) return gemm_form<RIGHT, TH, TD, 32>(t, rb, c, static_cast<int>(cb), lds);
   }
-  gemm_form<RIGHT, TH, TD, TO, 64>(t, rb, c, static_cast<int>(cb), lds);
+  gemm_form<RIGHT, TH, TD, 64>(t, rb, c, static_cast<int>(cb), lds);
 }
 
 // Copy a descriptor from global memory into LDS (8-byte words) after finding the task
@@ -358,18 +358,18 @@ __device__ inline int64_t load_task(const Task* __restrict__ tasks, int ntasks, 
 // Every workgroup serves one tile of one task; tasks of one launch may belong to
 // different updates (of different plans) and have different sizes.
 // Tile b of a batched contraction launch.
-template <bool RIGHT, typename TH, typename TD, typename TO>
+template <bool RIGHT, typename TH, typename TD>
 __device__ __forceinline__ void gemm_task_tile(const GemmTask* __restrict__ tasks, int ntasks, int64_t b, char* lds) {
   __shared__ __align__(16) char tbuf[sizeof(GemmTask)];      // raw storage: IndexMap has initialisers
   GemmTask& t = *reinterpret_cast<GemmTask*>(tbuf);
   const int64_t rel = load_task(tasks, ntasks, &t, b);
-  gemm_any<RIGHT, TH, TD, TO>(t, rel, lds);
+  gemm_any<RIGHT, TH, TD>(t, rel, lds);
 }
 
 // The tasks of a launch: a table in device memory, or (tasks null) one task passed by
 // value.  Its maps are indexed at run time, which the compiler would serve from a private
 // copy in scratch, so the workgroup copies it from the argument segment to LDS.
-template <bool RIGHT, typename TH, typename TD, typename TO>
+template <bool RIGHT, typename TH, typename TD>
 __global__ __launch_bounds__(256, 4) void hm_gemm(const GemmTask* __restrict__ tasks, int64_t ntasks, GemmTask) {
   extern __shared__ __align__(16) char tile_mem[];
   __shared__ __align__(16) char tbuf[sizeof(GemmTask)];      // raw storage: IndexMap has initialisers
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(256, 4) void hm_gemm(const GemmTask* __restrict__ t
       reinterpret_cast<uint64_t*>(tbuf)[w] = src[w];
     __syncthreads();
   }
-  gemm_any<RIGHT, TH, TD, TO>(t, rel, tile_mem);
+  gemm_any<RIGHT, TH, TD>(t, rel, tile_mem);
 }
 
 // part[c * stride + e] summed over c in [c0, c1) in the order of c: the loads go out
@@ -512,16 +512,16 @@ __global__ __launch_bounds__(256) void ingest_kernel(char* base) {
       const void* tasks = base + g.tasks;
       switch (g.kind) {
         case kSegRightRaw:
-          gemm_task_tile<true, TC, TC, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
+          gemm_task_tile<true, TC, TC>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
           break;
         case kSegLeftRaw:
-          gemm_task_tile<false, TC, TC, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
+          gemm_task_tile<false, TC, TC>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
           break;
         case kSegRightF64:
-          gemm_task_tile<true, double, double, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
+          gemm_task_tile<true, double, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
           break;
         case kSegLeftF64:
-          gemm_task_tile<false, double, double, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
+          gemm_task_tile<false, double, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
           break;
         case kSegFold:
           fold_task_tile(static_cast<const ReduceTask*>(tasks), g.ntasks, rel);
@@ -541,14 +541,14 @@ __global__ __launch_bounds__(256) void ingest_kernel(char* base) {
 
 // What a translation unit provides for its storage type T: the contraction launches with
 // raw operands of type T, and its ingest kernel.
-template <bool RIGHT, typename T, typename TO>
+template <bool RIGHT, typename T>
 void launch_tiles(const GemmTask* tasks, int nt, const GemmTask& one, int64_t blocks, size_t lds, hipStream_t st) {
-  hipLaunchKernelGGL((hm_gemm<RIGHT, T, T, TO>), dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, tasks,
+  hipLaunchKernelGGL((hm_gemm<RIGHT, T, T>), dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, tasks,
                      static_cast<int64_t>(nt), one);
 }
 using LaunchTiles = void (*)(const GemmTask*, int, const GemmTask&, int64_t, size_t, hipStream_t);
 struct TileKernels {
-  LaunchTiles right, left, left_f32;       // left_f32: FP32 results (FP64 operands only)
+  LaunchTiles right, left;
   const void* ingest;
 };
 TileKernels tile_kernels_f64();

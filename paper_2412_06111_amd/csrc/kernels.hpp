@@ -19,8 +19,7 @@ void launch_eye(int64_t n, double* o64, float* o32, uint16_t* o16, hipStream_t s
 //   RIGHT: out(c; i, j) = sum_{m in chunk c} Hm(m, i) D(drow(m), j),
 //          drow(m) = amap(m % L) + bmap(m / L)
 //   LEFT : out(c; m, j) = sum_{i in chunk c} Hm(m, i) D(drow(i), j),  drow(i) = amap(i)
-// D(row, j) = D[row * sDr + j * sDc] (dtype td).  Results are FP64 (or FP32 when
-// out_f32) stored at  out[c*cs + (row % Lo)*s0 + j*s1 + (row / Lo)*s2].
+// D(row, j) = D[row * sDr + j * sDc] (dtype td).  Results are FP64, stored at  out[c*cs + (row % Lo)*s0 + j*s1 + (row / Lo)*s2].
 struct OutLayout {
   int64_t Lo, s0, s1, s2, cs;
 };
@@ -50,7 +49,6 @@ struct GemmArgs {
   HMap hm;                     // operand addressing (packed unless a strided raw box)
   int nchunks = 1;
   void* out = nullptr;
-  bool out_f32 = false;
   OutLayout ol{};
 };
 // Returns the number of chunks actually written (<= a.nchunks); 0 if nothing to do.
@@ -98,7 +96,7 @@ struct BatchedGemm {
   std::vector<GemmTask> tasks;
   int64_t blocks = 0;
   size_t lds = 0;                          // dynamic LDS of the largest tile
-  bool right = true, out_f32 = false;
+  bool right = true;
   int th = TTNN_F64, td = TTNN_F64;
 };
 BatchedGemm plan_gemm_batched(const std::vector<GemmArgs>& args);
@@ -116,7 +114,7 @@ void launch_reduce_staged(const BatchedReduce& b, const ReduceTask* d_folds, con
 // per-level launches.  gl / level_end / rl as built for those launches (all plans of
 // compute dtype cd); sticky: each plan's sticky status word (set if a barrier wait ran
 // out).  Returns false, launching nothing, when the round does not fit the program
-// (too many phases, segments or plans, FP32 outputs) or the device cannot launch it.
+// (too many phases, segments or plans) or the device cannot launch it.
 constexpr int kIngestSegs = 4, kIngestPlans = 128, kIngestPhases = 48;
 enum : int32_t { kSegRightRaw = 0, kSegLeftRaw = 1, kSegRightF64 = 2, kSegLeftF64 = 3, kSegFold = 4, kSegReduce = 5 };
 bool launch_ingest(int cd, const std::vector<BatchedGemm>& gl, const std::vector<size_t>& level_end,
@@ -172,6 +170,10 @@ struct GJobList {
 // Launches every job (in chunks of kMaxGJobs per kernel, plus one combine launch for
 // the chunk's split contractions); `part` is split-contraction scratch.
 void launch_bgemm64(std::vector<GJob>& jobs, double* part, size_t part_elems, hipStream_t stream);
+
+// out[l + M j] = sum_{i < K} A[l + M i] B[j + N i] (FP64 products and sums), FP32 or FP64.
+void launch_outer64(const double* A, const double* B, int64_t M, int64_t N, int K, void* out, bool f32,
+                    hipStream_t stream);
 
 // ---------------------------------------------------------------- rank-1 updates
 // Kronecker vector over positions (first fastest): entry(row) = prod_p v[p][digit_p(row)].

@@ -57,3 +57,27 @@ def test_tile_ignores_values_past_the_box():
     torch.cuda.synchronize()
     errs = sketch_errors(plan, tree, sk)
     assert not failures(errs, TOL_ARITH["f32"]), errs
+
+
+# the reconstruction's last step (all modes but the last by the last): fewer rows or
+# columns than a wave's 64 x 32 tile, edges moved back inside it, ranks no multiple of 4,
+# and past the 1,024 rows of an XCD's share
+@pytest.mark.parametrize("dims,r", [((3, 5, 4), 1), ((9, 11, 37), 5), ((13, 5, 33), 4), ((16, 4, 32), 3),
+                                    ((64, 2, 31), 7), ((71, 19, 65), 18)])
+@pytest.mark.parametrize("out", ["f64", "f32"])
+def test_reconstruct_edges(dims, r, out):
+    import paper_2412_06111_amd as P
+    spec = (1, 2, 3)
+    tree = O.Tree(spec, dims, r, 0)
+    g = np.random.default_rng(sum(dims) + r)
+    cores = {n.id: g.standard_normal(O.core_shape(tree, n.id)) for n in tree.nodes}
+    want = O.reconstruct({i: c.ravel(order="F") if i == 0 else c for i, c in cores.items()}, tree)
+    plan = P.Plan(spec, dims, r, 0, variant="ttnn", dtype="f64", seed=1)
+    dev = [None] * plan.num_nodes
+    for n in tree.nodes:
+        dev[plan.node(n.modes)] = torch.from_numpy(cores[n.id].ravel(order="F").copy()).cuda()
+    got = plan.reconstruct(dev, out_dtype=P.F32 if out == "f32" else P.F64)
+    torch.cuda.synchronize()
+    err = np.linalg.norm(got.double().cpu().numpy() - want.ravel(order="F")) / np.linalg.norm(want)
+    assert err < (1e-12 if out == "f64" else 1e-7), err       # FP64 sums; FP32: one rounding of the result
+    plan.close()
