@@ -437,13 +437,41 @@ void record_box(Plan& P, const void* block, const int64_t* off, const int64_t* e
   left(group_args(before, P.nodes[rc.back()]), P.psi_root, 1, alpha);
 }
 
+// The levels of one update's steps (see run_box_ops_batched), each step given its slice of
+// the plan's partial scratch; returns their number.
+static int assign_levels(Plan& P, std::vector<BoxOp>& ops, std::vector<int>& level) {
+  level.assign(ops.size(), 0);
+  std::vector<const void*> written;
+  size_t used = 0;
+  int lv = 0;
+  for (size_t k = 0; k < ops.size(); ++k) {
+    BoxOp& op = ops[k];
+    const int nch = gemm_chunks(op.g, nullptr);
+    const size_t need = op.reduce && nch > 0 ? static_cast<size_t>(nch) * op.r.rows * op.r.ncols : 0;
+    const bool reads_level = std::find(written.begin(), written.end(), op.g.H) != written.end();
+    if (!written.empty() && (reads_level || used + need > P.partial_elems)) {
+      ++lv;
+      written.clear();
+      used = 0;
+    }
+    if (op.reduce) {
+      op.g.out = P.partial + used;
+      op.r.part = P.partial + used;
+      used += need;
+    }
+    written.push_back(op.reduce ? static_cast<const void*>(op.r.dst) : op.g.out);
+    level[k] = lv;
+  }
+  return lv + 1;
+}
+
 void run_box_ops_batched(const std::vector<Plan*>& plans, const std::vector<const std::vector<BoxOp>*>& items,
                          hipStream_t st) {
   // The steps of each update are grouped, in order, into levels: a step joins the
   // current level unless it reads a buffer that a step of the level writes, or its
   // partial sums no longer fit its plan's scratch next to those of the level (every step
   // gets its own slice).  Level l of every update in the call runs as one batched
-  // contraction launch per kind of step and one batched reduction launch; updates
+  // contraction launch per operand type and one batched reduction launch; updates
   // depend only on their own earlier levels.  Every step keeps its chunking and
   // summation order, so the results are bitwise those of running the steps one by one,
   // update by update.  All descriptor tables are built first and staged in one copy.
@@ -453,30 +481,7 @@ void run_box_ops_batched(const std::vector<Plan*>& plans, const std::vector<cons
   int nlev = 0;
   for (size_t u = 0; u < items.size(); ++u) {
     ops[u] = *items[u];
-    Plan& P = *plans[u];
-    level[u].assign(ops[u].size(), 0);
-    std::vector<const void*> written;
-    size_t used = 0;
-    int lv = 0;
-    for (size_t k = 0; k < ops[u].size(); ++k) {
-      BoxOp& op = ops[u][k];
-      const int nch = gemm_chunks(op.g, nullptr);
-      const size_t need = op.reduce && nch > 0 ? static_cast<size_t>(nch) * op.r.rows * op.r.ncols : 0;
-      const bool reads_level = std::find(written.begin(), written.end(), op.g.H) != written.end();
-      if (!written.empty() && (reads_level || used + need > P.partial_elems)) {
-        ++lv;
-        written.clear();
-        used = 0;
-      }
-      if (op.reduce) {
-        op.g.out = P.partial + used;
-        op.r.part = P.partial + used;
-        used += need;
-      }
-      written.push_back(op.reduce ? static_cast<const void*>(op.r.dst) : op.g.out);
-      level[u][k] = lv;
-    }
-    nlev = std::max(nlev, lv + 1);
+    nlev = std::max(nlev, assign_levels(*plans[u], ops[u], level[u]));
   }
   std::vector<BatchedGemm> gl;               // launch order: a level's kinds, then ...
   std::vector<BatchedReduce> rl;             // ... its reduction (one per level)
@@ -496,14 +501,14 @@ void run_box_ops_batched(const std::vector<Plan*>& plans, const std::vector<cons
         r.nchunks = nch;
         reds.push_back(r);
       }
-    // one launch per kind of contraction (right / left, operand and output types)
+    // one launch per operand type
     std::vector<bool> taken(gemms.size(), false);
     for (size_t a = 0; a < gemms.size(); ++a) {
       if (taken[a]) continue;
       std::vector<GemmArgs> kind;
       for (size_t b = a; b < gemms.size(); ++b) {
         const GemmArgs &x = gemms[a], &y = gemms[b];
-        if (taken[b] || x.right != y.right || x.th != y.th || x.td != y.td) continue;
+        if (taken[b] || x.th != y.th || x.td != y.td) continue;
         kind.push_back(y);
         taken[b] = true;
       }
@@ -565,6 +570,30 @@ void run_box_ops(Plan& P, const std::vector<BoxOp>& ops, hipStream_t st) {
 }
 
 namespace {
+// A packed whole tensor's steps level by level, every level's contractions in one launch
+// per operand type and its sums in another, the tables passed with the launches.  A 16^4
+// tensor's TTNN sketch is 5 launches instead of the 17 of a launch or two a node.
+void run_whole_ops(Plan& P, std::vector<BoxOp>& ops, hipStream_t st) {
+  std::vector<int> level;
+  const int nlev = assign_levels(P, ops, level);
+  std::vector<GemmArgs> gemms;
+  std::vector<ReduceTask> reds;
+  for (int lv = 0; lv < nlev; ++lv) {
+    gemms.clear();
+    reds.clear();
+    for (size_t k = 0; k < ops.size(); ++k) {
+      if (level[k] != lv) continue;
+      const int nch = gemm_chunks(ops[k].g, nullptr);
+      if (nch == 0) continue;
+      gemms.push_back(ops[k].g);
+      if (!ops[k].reduce) continue;
+      reds.push_back(ops[k].r);
+      reds.back().nchunks = nch;
+    }
+    launch_level_lin(gemms, reds, st);
+  }
+}
+
 void update_box_impl(Plan& P, const void* block, const int64_t* off, const int64_t* ext, const int64_t* strides,
                      double alpha, hipStream_t st) {
   P.epilogue_valid = false;
@@ -578,6 +607,18 @@ void update_box_impl(Plan& P, const void* block, const int64_t* off, const int64
     std::vector<BoxOp> ops;
     record_box(P, block, off, ext, strides, alpha, ops);
     run_box_ops(P, ops, st);
+    return;
+  }
+  // whole tensors for which the plan has no one-pass or MFMA form (small ones, and extents
+  // those forms do not cover): the generic steps of a box, level by level
+  if (P.whole_generic) {
+    if (P.timing) {
+      TTNN_HIP(hipEventRecord(P.sweep_ev[0], st));
+      P.sweep_recorded = false;
+    }
+    std::vector<BoxOp> ops;
+    record_box(P, block, off, ext, nullptr, alpha, ops);
+    run_whole_ops(P, ops, st);
     return;
   }
   fill_transposed(P, st);                       // the MFMA forms below read them

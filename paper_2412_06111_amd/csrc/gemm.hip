@@ -27,14 +27,49 @@ constexpr int kMinSteps = 8;          // and the least steps a chunk is worth (b
 
 // The kernels of a contraction's operand types: the raw block with the compute-type maps,
 // or an FP64 intermediate with the FP64 maps.
-LaunchTiles tiles_for(bool right, int th, int td) {
+TileKernels kernels_for(int th, int td) {
   TTNN_REQUIRE(th == td, TTNN_E_INVALID, "contraction operands of different types");
-  const TileKernels k = th == TTNN_F64 ? tile_kernels_f64() : th == TTNN_F32 ? tile_kernels_f32() : tile_kernels_bf16();
-  return right ? k.right : k.left;
+  return th == TTNN_F64 ? tile_kernels_f64() : th == TTNN_F32 ? tile_kernels_f32() : tile_kernels_bf16();
 }
 
 __global__ __launch_bounds__(256) void reduce_batched_kernel(const ReduceTask* __restrict__ tasks, int ntasks) {
   reduce_task_tile(tasks, ntasks, static_cast<int64_t>(blockIdx.x));
+}
+
+// The same two passes over tables passed with the launch (identity row maps).
+struct ReduceLinList {
+  ReduceLin t[kLinTasks];
+};
+__global__ __launch_bounds__(256) void reduce_lin_kernel(int64_t ntasks, ReduceLinList) {
+  __shared__ ReduceLin t;
+  const ReduceLin* tasks = (const ReduceLin*)((const char*)__builtin_amdgcn_kernarg_segment_ptr() + 8);
+  const int64_t rel = load_task(tasks, static_cast<int>(ntasks), &t, static_cast<int64_t>(blockIdx.x));
+  const int64_t total = t.rows * t.ncols;
+  for (int64_t e = rel * 256 + threadIdx.x; e < total; e += static_cast<int64_t>(t.nblocks) * 256) {
+    int64_t row, j;
+    split_at(e, t.ncols, j, row);
+    const double s = sum_chunks(t.part, 0, t.nchunks, t.cstride, e);
+    int64_t o;
+    if (t.mode == 0) {
+      o = row + t.ldr * j;
+    } else {
+      int64_t l, q;
+      split_at(row, t.L, l, q);
+      o = l + t.L * (j + t.kdim * q);
+    }
+    if (t.mode == 2) t.dst[o] = s;
+    else t.dst[o] += t.alpha * s;
+  }
+}
+// Groups of kFold chunks summed into each group's first slot; nblocks: element blocks.
+__global__ __launch_bounds__(256) void fold_lin_kernel(int64_t ntasks, ReduceLinList) {
+  __shared__ ReduceLin t;
+  const ReduceLin* tasks = (const ReduceLin*)((const char*)__builtin_amdgcn_kernarg_segment_ptr() + 8);
+  const int64_t rel = load_task(tasks, static_cast<int>(ntasks), &t, static_cast<int64_t>(blockIdx.x));
+  const int64_t E = t.rows * t.ncols;
+  const int64_t e = (rel % t.nblocks) * 256 + threadIdx.x;
+  const int c0 = static_cast<int>(rel / t.nblocks) * kFold, c1 = c0 + kFold < t.nchunks ? c0 + kFold : t.nchunks;
+  if (e < E) t.part[c0 * E + e] = sum_chunks(t.part, c0, c1, E, e);
 }
 
 __global__ __launch_bounds__(256) void fold_batched_kernel(const ReduceTask* __restrict__ tasks, int ntasks) {
@@ -196,6 +231,7 @@ static bool fill_task(const GemmArgs& a, GemmTask& t, size_t& lds) {
   t.ol = a.ol;
   t.tr = tile_rows(a.right, rows);
   t.ncb = ncb_of(t.tr, a.ncols);
+  t.right = a.right ? 1 : 0;
   t.row_blocks = (rows + t.tr - 1) / t.tr;
   t.nch = nch;
   t.col_blocks = col_blocks_of(t.tr, a.ncols);
@@ -209,19 +245,18 @@ int launch_gemm(const GemmArgs& a, hipStream_t st) {
   if (!fill_task(a, t, lds)) return 0;
   const int64_t blocks = t.row_blocks * t.nch * t.col_blocks;
   TTNN_REQUIRE(blocks < (int64_t(1) << 31), TTNN_E_INVALID, "contraction launch too large");
-  tiles_for(a.right, a.th, a.td)(nullptr, 0, t, blocks, lds, st);
+  kernels_for(a.th, a.td).table(nullptr, 0, t, blocks, lds, st);
   return static_cast<int>(t.nch);
 }
 
 BatchedGemm plan_gemm_batched(const std::vector<GemmArgs>& args) {
   BatchedGemm b;
   if (args.empty()) return b;
-  b.right = args[0].right;
   b.th = args[0].th;
   b.td = args[0].td;
   b.tasks.reserve(args.size());
   for (const GemmArgs& a : args) {
-    TTNN_REQUIRE(a.right == b.right && a.th == b.th && a.td == b.td, TTNN_E_INVALID,
+    TTNN_REQUIRE(a.th == b.th && a.td == b.td, TTNN_E_INVALID,
                  "batched contraction with mixed kinds");
     GemmTask t{};
     if (!fill_task(a, t, b.lds)) continue;
@@ -236,7 +271,7 @@ BatchedGemm plan_gemm_batched(const std::vector<GemmArgs>& args) {
 void launch_gemm_staged(const BatchedGemm& b, const GemmTask* d, hipStream_t st) {
   if (b.tasks.empty()) return;
   const int nt = static_cast<int>(b.tasks.size());
-  tiles_for(b.right, b.th, b.td)(d, nt, GemmTask{}, b.blocks, b.lds, st);
+  kernels_for(b.th, b.td).table(d, nt, GemmTask{}, b.blocks, b.lds, st);
 }
 
 void launch_gemm_batched(const std::vector<GemmArgs>& args, hipStream_t st) {
@@ -247,6 +282,66 @@ void launch_gemm_batched(const std::vector<GemmArgs>& args, hipStream_t st) {
       static_cast<const GemmTask*>(stage_descriptors(b.tasks.data(), b.tasks.size() * sizeof(GemmTask), st));
   launch_gemm_staged(b, d, st);
   fence_descriptors(st);
+}
+
+void launch_level_lin(const std::vector<GemmArgs>& args, const std::vector<ReduceTask>& reds, hipStream_t st) {
+  std::vector<bool> taken(args.size(), false);
+  for (size_t a = 0; a < args.size(); ++a) {              // one launch per operand type
+    if (taken[a]) continue;
+    std::vector<GemmLin> v;
+    size_t lds = 0;
+    int64_t blocks = 0;
+    auto flush = [&]() {
+      if (!v.empty()) kernels_for(args[a].th, args[a].td).lin(v.data(), static_cast<int>(v.size()), blocks, lds, st);
+      v.clear();
+      lds = 0;
+      blocks = 0;
+    };
+    for (size_t b = a; b < args.size(); ++b) {
+      if (taken[b] || args[b].th != args[a].th || args[b].td != args[a].td) continue;
+      taken[b] = true;
+      GemmTask t{};
+      if (!fill_task(args[b], t, lds)) continue;
+      const int64_t mine = t.row_blocks * t.nch * t.col_blocks;
+      TTNN_REQUIRE(!args[b].hm.strided && t.sDc == 1 && t.row_blocks < (int64_t(1) << 31) && t.nch < (int64_t(1) << 31) &&
+                       blocks + mine < (int64_t(1) << 31), TTNN_E_INVALID, "contraction launch too large");
+      v.push_back(GemmLin{t.H, t.D, t.out, t.L, t.n, t.Q, t.sDr, t.kchunk, t.ncols, t.tr, t.ncb, t.right,
+                          static_cast<int32_t>(blocks), static_cast<int32_t>(t.row_blocks), static_cast<int32_t>(t.nch),
+                          t.ol.cs == 0 ? 1 : 0});
+      blocks += mine;
+      if (v.size() == static_cast<size_t>(kLinTasks)) flush();
+    }
+    flush();
+  }
+  for (size_t i0 = 0; i0 < reds.size(); i0 += kLinTasks) {
+    ReduceLinList folds{}, tasks{};
+    int nf = 0, nt = 0;
+    int64_t fblocks = 0, blocks = 0;
+    for (size_t i = i0; i < std::min(reds.size(), i0 + kLinTasks); ++i) {
+      const ReduceTask& t = reds[i];
+      if (t.rows <= 0 || t.ncols <= 0 || t.nchunks <= 0) continue;
+      const int64_t E = t.rows * t.ncols;
+      ReduceLin r{t.part, t.dst, t.rows, t.ldr, t.L, t.kdim, E, t.alpha, t.nchunks, t.ncols, t.mode, 0, 0, 0};
+      if (fold_pays(t.nchunks, E)) {
+        ReduceLin f = r;
+        const int groups = (t.nchunks + kFold - 1) / kFold;
+        f.first_block = static_cast<int32_t>(fblocks);
+        f.nblocks = static_cast<int32_t>((E + 255) / 256);
+        fblocks += static_cast<int64_t>(f.nblocks) * groups;
+        folds.t[nf++] = f;
+        r.nchunks = groups;
+        r.cstride = E * kFold;
+      }
+      r.first_block = static_cast<int32_t>(blocks);
+      r.nblocks = grid_for(E);
+      blocks += r.nblocks;
+      tasks.t[nt++] = r;
+    }
+    if (nf) hipLaunchKernelGGL(fold_lin_kernel, dim3(static_cast<unsigned>(fblocks)), dim3(256), 0, st,
+                               static_cast<int64_t>(nf), folds);
+    if (nt) hipLaunchKernelGGL(reduce_lin_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st,
+                               static_cast<int64_t>(nt), tasks);
+  }
 }
 
 BatchedReduce plan_reduce_batched(const std::vector<ReduceTask>& in) {
@@ -392,8 +487,8 @@ bool launch_ingest(int cd, const std::vector<BatchedGemm>& gl, const std::vector
       lds = std::max(lds, b.lds);
       if (ph.nseg == kIngestSegs) return false;
       int kind;
-      if (b.th == cd && b.td == cd) kind = b.right ? kSegRightRaw : kSegLeftRaw;
-      else if (b.th == TTNN_F64 && b.td == TTNN_F64) kind = b.right ? kSegRightF64 : kSegLeftF64;
+      if (b.th == cd && b.td == cd) kind = kSegRaw;
+      else if (b.th == TTNN_F64 && b.td == TTNN_F64) kind = kSegF64;
       else return false;
       IngestSeg& g = ph.seg[ph.nseg++];
       g.kind = kind;

@@ -4,8 +4,7 @@
 namespace ttnn {
 
 TileKernels tile_kernels_bf16() {
-  return TileKernels{launch_tiles<true, uint16_t>, launch_tiles<false, uint16_t>,
-                     reinterpret_cast<const void*>(ingest_kernel<uint16_t>)};
+  return TileKernels{launch_tiles<uint16_t>, launch_tiles_lin<uint16_t>, reinterpret_cast<const void*>(ingest_kernel<uint16_t>)};
 }
 
 }  // namespace ttnn

@@ -4,8 +4,7 @@
 namespace ttnn {
 
 TileKernels tile_kernels_f32() {
-  return TileKernels{launch_tiles<true, float>, launch_tiles<false, float>,
-                     reinterpret_cast<const void*>(ingest_kernel<float>)};
+  return TileKernels{launch_tiles<float>, launch_tiles_lin<float>, reinterpret_cast<const void*>(ingest_kernel<float>)};
 }
 
 }  // namespace ttnn

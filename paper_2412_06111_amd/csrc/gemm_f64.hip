@@ -4,8 +4,7 @@
 namespace ttnn {
 
 TileKernels tile_kernels_f64() {
-  return TileKernels{launch_tiles<true, double>, launch_tiles<false, double>,
-                     reinterpret_cast<const void*>(ingest_kernel<double>)};
+  return TileKernels{launch_tiles<double>, launch_tiles_lin<double>, reinterpret_cast<const void*>(ingest_kernel<double>)};
 }
 
 }  // namespace ttnn

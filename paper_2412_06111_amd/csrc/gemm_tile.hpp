@@ -3,6 +3,7 @@
 // the fixed-order sums of chunk partials and the persistent ingest kernel.
 #pragma once
 
+#include <cstring>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -316,16 +317,16 @@ __device__ __forceinline__ void gemm_form(const GemmTask& t, int64_t rb, int64_t
   else if (ncb == 2) gemm_tile<RIGHT, TH, TD, TR, 2>(t, rb * TR, c, j0, lds);
   else if constexpr (TR == 64) gemm_tile<RIGHT, TH, TD, TR, 3>(t, rb * TR, c, j0, lds);
 }
-template <bool RIGHT, typename TH, typename TD>
+template <typename TH, typename TD>
 __device__ __forceinline__ void gemm_any(const GemmTask& t, int64_t rel, char* lds) {
   int64_t rb, c, cb;
   split_at(rel, t.row_blocks, rb, rel);
   split_at(rel, t.nch, c, cb);
-  if constexpr (RIGHT) {
-    if (t.tr == 16) return gemm_form<RIGHT, TH, TD, 16>(t, rb, c, static_cast<int>(cb), lds);
-    if (t.tr == 32) return gemm_form<RIGHT, TH, TD, 32>(t, rb, c, static_cast<int>(cb), lds);
-  }
-  gemm_form<RIGHT, TH, TD, 64>(t, rb, c, static_cast<int>(cb), lds);
+  const int jb = static_cast<int>(cb);
+  if (!t.right) gemm_form<false, TH, TD, 64>(t, rb, c, jb, lds);
+  else if (t.tr == 16) gemm_form<true, TH, TD, 16>(t, rb, c, jb, lds);
+  else if (t.tr == 32) gemm_form<true, TH, TD, 32>(t, rb, c, jb, lds);
+  else gemm_form<true, TH, TD, 64>(t, rb, c, jb, lds);
 }
 
 // Copy a descriptor from global memory into LDS (8-byte words) after finding the task
@@ -358,32 +359,69 @@ __device__ inline int64_t load_task(const Task* __restrict__ tasks, int ntasks, 
 // Every workgroup serves one tile of one task; tasks of one launch may belong to
 // different updates (of different plans) and have different sizes.
 // Tile b of a batched contraction launch.
-template <bool RIGHT, typename TH, typename TD>
+template <typename TH, typename TD>
 __device__ __forceinline__ void gemm_task_tile(const GemmTask* __restrict__ tasks, int ntasks, int64_t b, char* lds) {
   __shared__ __align__(16) char tbuf[sizeof(GemmTask)];      // raw storage: IndexMap has initialisers
   GemmTask& t = *reinterpret_cast<GemmTask*>(tbuf);
   const int64_t rel = load_task(tasks, ntasks, &t, b);
-  gemm_any<RIGHT, TH, TD>(t, rel, lds);
+  gemm_any<TH, TD>(t, rel, lds);
 }
 
-// The tasks of a launch: a table in device memory, or (tasks null) one task passed by
-// value.  Its maps are indexed at run time, which the compiler would serve from a private
-// copy in scratch, so the workgroup copies it from the argument segment to LDS.
-template <bool RIGHT, typename TH, typename TD>
-__global__ __launch_bounds__(256, 4) void hm_gemm(const GemmTask* __restrict__ tasks, int64_t ntasks, GemmTask) {
+// The tasks of a launch: a table in device memory (ntasks > 0), one task passed by value
+// (0), or -ntasks linear ones passed by value; right and left ones side by side.  A task's maps are indexed at run time,
+// which the compiler would serve from a private copy in scratch, so the workgroup copies
+// the task from the argument segment to LDS.
+struct GemmByValue {
+  union {
+    char one[sizeof(GemmTask)];
+    GemmLin lin[kLinTasks];
+  };
+};
+template <typename TH, typename TD>
+__global__ __launch_bounds__(256, 4) void hm_gemm(const GemmTask* __restrict__ tasks, int64_t ntasks, GemmByValue) {
   extern __shared__ __align__(16) char tile_mem[];
   __shared__ __align__(16) char tbuf[sizeof(GemmTask)];      // raw storage: IndexMap has initialisers
   GemmTask& t = *reinterpret_cast<GemmTask*>(tbuf);
   int64_t rel = static_cast<int64_t>(blockIdx.x);
-  if (tasks) {
+  const char* args = (const char*)__builtin_amdgcn_kernarg_segment_ptr() + 16;   // past the two scalars
+  if (ntasks > 0) {
     rel = load_task(tasks, static_cast<int>(ntasks), &t, rel);
-  } else {
-    const uint64_t* src = (const uint64_t*)__builtin_amdgcn_kernarg_segment_ptr() + 2;   // past the two scalars
+  } else if (ntasks == 0) {
     for (int w = threadIdx.x; w < static_cast<int>(sizeof(GemmTask) / 8); w += 256)
-      reinterpret_cast<uint64_t*>(tbuf)[w] = src[w];
+      reinterpret_cast<uint64_t*>(tbuf)[w] = reinterpret_cast<const uint64_t*>(args)[w];
+    __syncthreads();
+  } else {
+    __shared__ GemmLin lin;
+    rel = load_task(reinterpret_cast<const GemmLin*>(args), static_cast<int>(-ntasks), &lin, rel);
+    if (threadIdx.x == 0) {
+      t.H = lin.H;
+      t.D = lin.D;
+      t.out = lin.out;
+      t.L = lin.L;
+      t.n = lin.n;
+      t.Q = lin.Q;
+      t.sDr = lin.sDr;
+      t.sDc = 1;
+      t.kchunk = lin.kchunk;
+      t.row_blocks = lin.row_blocks;
+      t.nch = lin.nch;
+      t.ncols = lin.ncols;
+      t.tr = lin.tr;
+      t.ncb = lin.ncb;
+      t.right = lin.right;
+      // the DRM row of (l, q) is l + L q, of a left value the value itself
+      t.amap.n = t.bmap.n = 1;
+      t.amap.ext[0] = t.bmap.ext[0] = INT64_MAX;
+      t.amap.off[0] = t.bmap.off[0] = 0;
+      t.amap.stride[0] = 1;
+      t.bmap.stride[0] = lin.L;
+      t.hm.strided = 0;
+      t.ol = lin.store ? OutLayout{lin.L, 1, lin.L, lin.L * lin.ncols, 0}
+                       : OutLayout{INT64_MAX, lin.ncols, 1, 0, (lin.right ? lin.n : lin.L * lin.Q) * lin.ncols};
+    }
     __syncthreads();
   }
-  gemm_any<RIGHT, TH, TD>(t, rel, tile_mem);
+  gemm_any<TH, TD>(t, rel, tile_mem);
 }
 
 // part[c * stride + e] summed over c in [c0, c1) in the order of c: the loads go out
@@ -511,17 +549,11 @@ __global__ __launch_bounds__(256) void ingest_kernel(char* base) {
       const IngestSeg& g = P.seg[s];
       const void* tasks = base + g.tasks;
       switch (g.kind) {
-        case kSegRightRaw:
-          gemm_task_tile<true, TC, TC>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
+        case kSegRaw:
+          gemm_task_tile<TC, TC>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
           break;
-        case kSegLeftRaw:
-          gemm_task_tile<false, TC, TC>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
-          break;
-        case kSegRightF64:
-          gemm_task_tile<true, double, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
-          break;
-        case kSegLeftF64:
-          gemm_task_tile<false, double, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
+        case kSegF64:
+          gemm_task_tile<double, double>(static_cast<const GemmTask*>(tasks), g.ntasks, rel, tile_mem);
           break;
         case kSegFold:
           fold_task_tile(static_cast<const ReduceTask*>(tasks), g.ntasks, rel);
@@ -541,14 +573,25 @@ __global__ __launch_bounds__(256) void ingest_kernel(char* base) {
 
 // What a translation unit provides for its storage type T: the contraction launches with
 // raw operands of type T, and its ingest kernel.
-template <bool RIGHT, typename T>
+template <typename T>
 void launch_tiles(const GemmTask* tasks, int nt, const GemmTask& one, int64_t blocks, size_t lds, hipStream_t st) {
-  hipLaunchKernelGGL((hm_gemm<RIGHT, T, T>), dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, tasks,
-                     static_cast<int64_t>(nt), one);
+  GemmByValue v{};
+  if (!tasks) std::memcpy(v.one, &one, sizeof(one));
+  hipLaunchKernelGGL((hm_gemm<T, T>), dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, tasks,
+                     static_cast<int64_t>(tasks ? nt : 0), v);
+}
+template <typename T>
+void launch_tiles_lin(const GemmLin* tasks, int nt, int64_t blocks, size_t lds, hipStream_t st) {
+  GemmByValue v{};
+  std::memcpy(v.lin, tasks, static_cast<size_t>(nt) * sizeof(GemmLin));
+  hipLaunchKernelGGL((hm_gemm<T, T>), dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, nullptr,
+                     static_cast<int64_t>(-nt), v);
 }
 using LaunchTiles = void (*)(const GemmTask*, int, const GemmTask&, int64_t, size_t, hipStream_t);
+using LaunchLin = void (*)(const GemmLin*, int, int64_t, size_t, hipStream_t);
 struct TileKernels {
-  LaunchTiles right, left;
+  LaunchTiles table;
+  LaunchLin lin;
   const void* ingest;
 };
 TileKernels tile_kernels_f64();

@@ -71,7 +71,7 @@ struct GemmTask {
   IndexMap amap, bmap;
   HMap hm;
   OutLayout ol;
-  int32_t ncols, tr, ncb, pad_;            // tr x 16 ncb: the tile
+  int32_t ncols, tr, ncb, right;           // tr x 16 ncb: the tile
 };
 struct ReduceTask {
   double* part = nullptr;
@@ -83,8 +83,26 @@ struct ReduceTask {
   int64_t cstride = 0;                     // distance between chunk partials (0: rows * ncols)
   int32_t nchunks = 0, ncols = 0, mode = 0, groups = 0;
 };
-// Launch the same kind of generic contraction (right/left, dtypes, output type) for
-// every element of `args` in one kernel: each workgroup serves one tile of one task.
+// Descriptors of packed whole-tensor contractions (maps linear in the contraction index,
+// results as chunk partials or, left, stored in place), small enough to be passed with the
+// launch: nothing is staged, so a captured launch replays with its own arguments.
+struct GemmLin {
+  const void* H;
+  const void* D;
+  void* out;
+  int64_t L, n, Q, sDr, kchunk;
+  int32_t ncols, tr, ncb, right;
+  int32_t first_block, row_blocks, nch, store;
+};
+struct ReduceLin {
+  double* part;
+  double* dst;
+  int64_t rows, ldr, L, kdim, cstride;
+  double alpha;
+  int32_t nchunks, ncols, mode, first_block, nblocks, pad_;
+};
+constexpr int kLinTasks = 24;
+// Launch the generic contractions of one operand type (right and left) for every element of `args` in one kernel: each workgroup serves one tile of one task.
 // Results are bitwise those of launch_gemm on each element.
 void launch_gemm_batched(const std::vector<GemmArgs>& args, hipStream_t stream);
 // Fixed-order partial sums of several contractions in one launch (see launch_reduce).
@@ -96,7 +114,6 @@ struct BatchedGemm {
   std::vector<GemmTask> tasks;
   int64_t blocks = 0;
   size_t lds = 0;                          // dynamic LDS of the largest tile
-  bool right = true;
   int th = TTNN_F64, td = TTNN_F64;
 };
 BatchedGemm plan_gemm_batched(const std::vector<GemmArgs>& args);
@@ -108,6 +125,10 @@ struct BatchedReduce {
 BatchedReduce plan_reduce_batched(const std::vector<ReduceTask>& tasks);
 void launch_reduce_staged(const BatchedReduce& b, const ReduceTask* d_folds, const ReduceTask* d_tasks,
                           hipStream_t stream);
+// The same from tables passed with the launches (at most kLinTasks a launch): contractions
+// of one operand type, right and left side by side, then their reductions.  The callers'
+// maps must be the linear ones of a packed whole tensor.
+void launch_level_lin(const std::vector<GemmArgs>& args, const std::vector<ReduceTask>& reds, hipStream_t stream);
 // Persistent ingest: every phase of a batched round of box updates in one cooperative
 // launch (level by level: the contractions of all kinds, the chunk folds, the
 // reductions; grid-wide barriers between phases), bitwise the same results as the
@@ -116,7 +137,7 @@ void launch_reduce_staged(const BatchedReduce& b, const ReduceTask* d_folds, con
 // out).  Returns false, launching nothing, when the round does not fit the program
 // (too many phases, segments or plans) or the device cannot launch it.
 constexpr int kIngestSegs = 4, kIngestPlans = 128, kIngestPhases = 48;
-enum : int32_t { kSegRightRaw = 0, kSegLeftRaw = 1, kSegRightF64 = 2, kSegLeftF64 = 3, kSegFold = 4, kSegReduce = 5 };
+enum : int32_t { kSegRaw = 0, kSegF64 = 1, kSegFold = 2, kSegReduce = 3 };
 bool launch_ingest(int cd, const std::vector<BatchedGemm>& gl, const std::vector<size_t>& level_end,
                    const std::vector<BatchedReduce>& rl, const std::vector<int*>& sticky, hipStream_t stream);
 // Copy `bytes` of host descriptors into device memory that stays valid for work

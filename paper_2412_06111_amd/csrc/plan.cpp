@@ -481,6 +481,11 @@ std::unique_ptr<Plan> build_plan(const ttnn_problem* pr, hipStream_t stream, boo
   }
   if (P->allow_fused) fused_prepare(*P, stream);
   plan_xt(true);
+  // (chain heads past mode 1 of large tensors, from other visiting orders or free modes,
+  // have a streaming mode product)
+  P->whole_generic = !kr && !P->fused.enabled &&
+                     (P->N < (int64_t(1) << 22) || (P->lex && P->nodes.size() == static_cast<size_t>(nn)));
+  for (const Node& nd : P->nodes) P->whole_generic = P->whole_generic && !nd.Xt && !nd.Yt && !nd.Xt64;
   zero_accumulators(*P, stream);
   TTNN_HIP(hipGetLastError());
   return P;

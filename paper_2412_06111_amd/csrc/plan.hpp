@@ -108,6 +108,7 @@ struct Plan {
   FusedT4 fused;
   bool allow_fused = true;                 // off: every update takes the generic path
   bool lex = true;                         // STTNN visits the children left to right
+  bool whole_generic = false;              // no one-pass or MFMA form serves a whole tensor
   // measurement hook: events around the sweep of the last update (see ttnn_set_timing)
   bool timing = false;
   hipEvent_t sweep_ev[2] = {nullptr, nullptr};
