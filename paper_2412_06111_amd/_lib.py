@@ -158,9 +158,17 @@ class _nullctx:
         return False
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def stream_ptr(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    """Handle of `stream`, or of the current stream (without building a Stream object
+    where torch offers that: 1 us of every call)."""
+    if stream is not None:
+        return C.c_void_p(stream.cuda_stream)
+    if _raw_stream is not None:
+        return C.c_void_p(_raw_stream(torch.cuda.current_device()))
+    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
 # ---------------------------------------------------------------- trees
@@ -341,6 +349,7 @@ class Plan:
         self.node_modes = modes
         self.node_of_modes = {m: i for i, m in enumerate(modes)}
         self.num_nodes = len(modes)
+        self._shapes = {}                    # (node, kind) -> sketch shape (fixed by the problem)
         self.handle = C.c_void_p()
         self.workspace = None
         if pool:
@@ -541,15 +550,18 @@ class Plan:
 
     # ------------------------------------------------------------ readbacks
     def sketch_shape(self, node, kind):
-        r, c = C.c_int64(), C.c_int64()
-        check(lib.ttnn_sketch_shape(self.handle, node, kind, C.byref(r), C.byref(c)))
-        return r.value, c.value
+        shape = self._shapes.get((node, kind)) if self.handle else None
+        if shape is None:
+            r, c = C.c_int64(), C.c_int64()
+            check(lib.ttnn_sketch_shape(self.handle, node, kind, C.byref(r), C.byref(c)))
+            shape = self._shapes[node, kind] = r.value, c.value
+        return shape
 
     def read_sketch(self, node, kind, stream=None):
         r, c = self.sketch_shape(node, kind)
-        out = torch.empty(r * c, dtype=torch.float64, device="cuda")
-        check(lib.ttnn_read_sketch(self.handle, node, kind, C.c_void_p(out.data_ptr()), stream_ptr(stream)))
-        return out.view(c, r).t()        # column-major (r x c)
+        out = torch.empty((c, r), dtype=torch.float64, device="cuda")
+        check(lib.ttnn_read_sketch(self.handle, node, kind, out.data_ptr(), stream_ptr(stream)))
+        return out.t()                   # column-major (r x c)
 
     def drm_shape(self, node, kind):
         r, c = C.c_int64(), C.c_int64()
@@ -654,12 +666,13 @@ def update_batched(items, stream=None):
         check_block(block, plan.torch_dtype, extent, plan.d, strides)
         if len(offset) != plan.d:
             raise ValueError(f"item {i}: offset has {len(offset)} modes, the tensor has {plan.d}")
-        arr[i].plan = plan.handle
-        arr[i].d_block = C.c_void_p(block.data_ptr())
-        for mu in range(plan.d):
-            arr[i].offset[mu] = int(offset[mu])
-            arr[i].extent[mu] = int(extent[mu])
-            arr[i].strides[mu] = 0 if strides is None else int(strides[mu])
-        arr[i].alpha = float(alpha)
+        a, d = arr[i], plan.d
+        a.plan = plan.handle
+        a.d_block = block.data_ptr()
+        a.offset[:d] = [int(o) for o in offset]
+        a.extent[:d] = [int(e) for e in extent]
+        if strides is not None:
+            a.strides[:d] = [int(x) for x in strides]
+        a.alpha = float(alpha)
         keep.append(block)
     check(lib.ttnn_sketch_update_batched(len(items), arr, stream_ptr(stream)))
