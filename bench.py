@@ -27,6 +27,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "sketch ingest GB/s (% HBM roofline) + p50/p99 update latency, bf16/fp32 vs fp64"
 HBM_PEAK_GBS = 8000.0
+# FP32 rates are given against the FP32 MFMA also where a kernel forms its FP32 products as
+# six BF16 ones (the sweep at r = 32), which can take a fraction above 1
 MFMA_PEAK_TFLOPS = {"bf16": 2516.6, "f32": 157.3, "f64": 78.6}
 ESIZE = {"f64": 8, "f32": 4, "bf16": 2}
 

@@ -42,6 +42,8 @@ struct SttnnArgs {
   const void *XA, *X1, *YA, *Y1, *X2, *XB;
   void *PRA, *PZA, *PR1, *PR2, *PRB;
   void* Z1;            // Z1-out mode: Y_1^T slab for every (i_2, column), [i_2][i_B][j1]
+  const uint16_t *YA3, *Y13, *XB3;          // sttnn_t4_x3_kernel: Y_A, Y_1, X_B as three BF16 planes
+  uint32_t* redo;      // ... and, per tile and wave, whether sttnn_t4_kernel has to form the tile again
 };
 
 // Wide fragment: V = 16 / sizeof(T) consecutive contraction values of one lane (one
@@ -146,14 +148,15 @@ struct Swz {
 // Copy `rows` rows of RL elements (row r from g + r*gs) into LDS at l, swizzled:
 // each instruction fills 64 / CPR whole rows (64 lanes x 16 bytes, one contiguous
 // kilobyte of LDS); lane L fetches the chunk that belongs at its position.
-// Instructions are dealt to the eight waves; the LDS address is wave-uniform.
-template <typename T, int RL>
+// Instructions are dealt to NW waves, of which this is number `wave`; the LDS address is
+// wave-uniform.
+template <typename T, int RL, int NW = kThreadsF / 64>
 __device__ inline void lds_dma_rows(const T* g, int64_t gs, T* l, int rows, int wave, int lane) {
   using Z = Swz<T, RL>;
   constexpr int RPI = 64 / Z::CPR;                    // rows per instruction
   const int ninstr = rows / RPI;
   const int rl = lane / Z::CPR, p = lane % Z::CPR;
-  for (int q = wave; q < ninstr; q += kThreadsF / 64) {
+  for (int q = wave; q < ninstr; q += NW) {
     const int r = q * RPI + rl;
     const int c = p ^ (r & Z::MASK);
     lds_dma16(g + r * gs + static_cast<int64_t>(c) * Z::EV, l + q * RPI * RL);
@@ -234,6 +237,9 @@ __device__ inline void bd_chain(const typename P::T* Ms, int iBl, int lg, LoadA&
   }
 }
 
+// The FP32 forms at r = 32 whose products are split into BF16 ones (sttnn_t4_x3_kernel).
+constexpr bool split_form(int dt, int R, bool tt, bool zout) { return dt == TTNN_F32 && R == 32 && (tt || zout); }
+
 // ZO (STTNN only): instead of contracting Z1 with X_2 in the tile (which re-reads the
 // X_2 rows of the column band in every row tile), write Z1 out; R_2 is then one
 // streaming contraction that reads X_2 once (used for r >= 32).
@@ -281,6 +287,12 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_kernel(SttnnArgs a) {
   T* Z1lo = reinterpret_cast<T*>(smem + Lay::OFF_Z1) + B2 * Lay::ZS;   // ZH: the low halves
   T* Y1s = reinterpret_cast<T*>(smem + Lay::OFF_Y1);
 
+  if constexpr (split_form(DT, R, TT, ZO)) {     // behind sttnn_t4_x3_kernel: the tiles that it marked
+    uint32_t again = 0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) again |= a.redo[8 * blockIdx.x + w];
+    if (!__builtin_amdgcn_readfirstlane(again)) return;
+  }
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
 
@@ -708,6 +720,414 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_kernel(SttnnArgs a) {
   }
 }
 
+// ---------------------------------------------------------------- FP32 at r = 32 on BF16 products
+// An FP32 value is the exact sum of three BF16 ones, x = h + m + l (h = RNE(x), m = RNE(x -
+// h), l the rest: 8 + 8 + 8 bits), so an FP32 product is a sum of BF16 products, of which
+// h h', h m', m h', h l', l h', m m' are formed (the rest is below 2^-24 |x x'|), each
+// exact, accumulated in FP32 like the FP32 products they stand for.  Six 16x16x32 BF16
+// MFMAs take 0.375 of the time of the eight 16x16x4 FP32 ones: the 85.9 GFLOP of a 128^4
+// sweep, 546 us on the FP32 MFMA, 205 us, which leaves the sweep to its bytes (1.95 GB:
+// T, X_1, Z_1 and the partials).
+//
+// The tile and the results are those of sttnn_t4_kernel with two slabs a tile and 32-column
+// sub-tiles.  Waves 4-7 take (a) R_A and (c) R_1, 32 rows of i1 each; waves 0, 1 (b) Z_A and
+// waves 2, 3 (d1) Z_1 (TT: (b') R_B^T), 16 columns each.  The slab's values are split in
+// registers as they are read (5.5 vector instructions a value); the Y_A, Y_1 and X_B rows,
+// read by every sub-tile, are split once in a plan ([3][row][i1] planes): Y_A stays in LDS
+// for the tile, Y_1 or X_B in the registers of waves 2, 3.  X_A and X_1 come from global
+// memory a column block ahead into the registers of waves 4-7 and are split there (a split
+// copy of X_1 would add 134 MB to the sweep's bytes).  That leaves room for four stages of T:
+// waves 0, 1, which load nothing else, issue the slab's copies three sub-tiles ahead.
+//
+// 128^4, r = 32, whole update, in turns with the FP32 MFMA form: STTNN 1028 -> 807 us, TTNN
+// 1648 -> 1432 us (with two stages, Y_1 in LDS and the copies issued by all waves 1003 and
+// 1512).  The sketches' errors against FP64 are below those of the FP32 MFMA form (R_1 of a
+// 128^4 tensor 3e-7, there 1.6e-6).
+//
+// A tile with results outside the range where the split is exact (SplitRange) is marked, and
+// sttnn_t4_kernel, launched behind this kernel, forms it again; with no mark that launch
+// takes 4 us.
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+struct Bf3 {
+  bf16x8_t p[3];      // h, m, l
+};
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+  const f32x2_t v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+__device__ __forceinline__ Bf3 split3(const float (&x)[8]) {
+  u32x4_t h, m, l;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    h[i] = bf16_pair(x[2 * i], x[2 * i + 1]);
+    const float r0 = x[2 * i] - __uint_as_float(h[i] << 16), r1 = x[2 * i + 1] - __uint_as_float(h[i] & 0xFFFF0000u);
+    m[i] = bf16_pair(r0, r1);
+    l[i] = bf16_pair(r0 - __uint_as_float(m[i] << 16), r1 - __uint_as_float(m[i] & 0xFFFF0000u));
+  }
+  return Bf3{{__builtin_bit_cast(bf16x8_t, h), __builtin_bit_cast(bf16x8_t, m), __builtin_bit_cast(bf16x8_t, l)}};
+}
+// The six products, smallest first, onto NB accumulators in turn (neighbouring products
+// then do not wait for one another).
+template <int NB>
+__device__ __forceinline__ void mfma3(const Bf3 (&a)[NB], const Bf3& b, f32x4_t (&acc)[NB]) {
+  constexpr int A[6] = {1, 2, 0, 1, 0, 0}, B[6] = {1, 0, 2, 0, 1, 0};
+#pragma unroll
+  for (int q = 0; q < 6; ++q)
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i].p[A[q]], b.p[B[q]], acc[i], 0, 0, 0);
+}
+
+struct X3Layout {
+  static constexpr int R = 32, KP = 48, B2 = 2, SC = 32, NST = 4;
+  static constexpr size_t MS = size_t(SC) * N1 * 4;           // one stage of T
+  static constexpr int YROWS = 3 * KP;                        // resident rows a slab: Y_A planes
+  static constexpr size_t OFF_YR = NST * MS;
+  static constexpr size_t TOTAL = OFF_YR + size_t(B2) * YROWS * N1 * 2;
+  static_assert(TOTAL <= 160 * 1024, "LDS");
+};
+
+// Whether results leave the range of the split: infinite or NaN (an infinity, or an FP32
+// value above the largest BF16 one, splits into NaN), or so small that a part of the split
+// may have fallen below the smallest BF16 number.
+struct SplitRange {
+  uint32_t least = 0xFFFFFFFFu;             // twice the bits of the smallest magnitude, less one: zero is greatest
+  float nan = 0.f;                          // NaN from the first infinity or NaN on
+  __device__ __forceinline__ void add(const f32x4_t& x) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      least = min(least, (__float_as_uint(x[v]) << 1) - 1);
+      nan = __builtin_fmaf(x[v], 0.f, nan);
+    }
+  }
+  __device__ __forceinline__ bool left() const {
+    constexpr uint32_t kLeast = uint32_t(127 - 80) << 24;      // 2^-80, twice its bits
+    return __any(nan != nan || least < kLeast);
+  }
+};
+
+template <bool TT>
+__global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
+  using Lay = X3Layout;
+  constexpr int R = Lay::R, KP = Lay::KP, B2 = Lay::B2, SC = Lay::SC, NST = Lay::NST;
+  constexpr int CBR = R / 16, KB = KP / 16, NCB = SC / 16, NK = N1 / 32;
+  using ZN = Swz<float, N1>;
+  using ZY = Swz<uint16_t, N1>;
+  __shared__ __align__(16) char smem[Lay::TOTAL];
+  uint16_t* YRs = reinterpret_cast<uint16_t*>(smem + Lay::OFF_YR);
+
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tA, tB;                               // as in sttnn_t4_kernel
+  {
+    const int w = blockIdx.x;
+    if (a.TA % 8 == 0) {
+      const int x = w % 8, j = w / 8, gpx = a.TA / 8;
+      tA = x * gpx + j % gpx;
+      tB = j / gpx;
+    } else if (a.TB % 8 == 0) {
+      const int x = w % 8, j = w / 8, bpx = a.TB / 8;
+      tB = x * bpx + j / a.TA;
+      tA = j % a.TA;
+    } else {
+      tB = w / a.TA;
+      tA = w % a.TA;
+    }
+  }
+  const int64_t i2_0 = static_cast<int64_t>(tA) * B2;
+  const int64_t c_tile = static_cast<int64_t>(tB) * a.CB * SC;
+  const int64_t nA = a.nA, nB = a.nB, n2 = a.n2;
+  const float* T = static_cast<const float*>(a.T);
+  const float* XA = static_cast<const float*>(a.XA);
+  const float* X1 = static_cast<const float*>(a.X1);
+  const bool bd = wave < 4;                 // (b)/(d1) waves; the others (a)/(c)
+  const int nsub = a.CB * B2;
+
+  auto stage = [&](int s) { return reinterpret_cast<float*>(smem + (s % NST) * Lay::MS); };
+  // Waves 0, 1: the slab's copy of sub-tile s (or, past the last, of the last one into a
+  // stage that nobody reads: the copies in flight are then the same in every sub-tile, and
+  // a wait can count them), eight loads a wave.
+  auto issue = [&](int s) {
+    constexpr int RPI = 64 / ZN::CPR;       // rows a load
+    static_assert(SC == 16 * RPI, "eight loads a wave");
+    const int e = s < nsub ? s : nsub - 1;
+    const float* g = T + (i2_0 + e % B2) * N1 + nA * (c_tile + static_cast<int64_t>(e / B2) * SC);
+    float* l = stage(s);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int q = 2 * u + wave, r = q * RPI + lane / ZN::CPR;
+      lds_dma16(g + r * nA + ((lane % ZN::CPR) ^ (r & ZN::MASK)) * ZN::EV, l + q * RPI * N1);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < B2; ++i)
+    lds_dma_rows<uint16_t, N1>(a.YA3 + (i2_0 + i) * N1, nA, YRs + i * Lay::YROWS * N1,
+                               3 * KP, wave, lane);
+  __syncthreads();                          // the resident rows are there
+
+  static_assert(B2 == 2, "the loops' slabs");
+  // A barrier without the fence of __syncthreads, which would wait for every copy in flight;
+  // the LDS reads before it are waited for, and no access moves across it.
+  auto barrier = [&]() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  auto next_stage = [&]() {
+    lds_wait_all();                         // this wave's reads of the last stage are done
+    barrier();
+  };
+  // The roles run loops of their own, so that neither's registers are held through the
+  // other's code; both pass one barrier a sub-tile.
+  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+  SplitRange range;
+  auto mark = [&]() {
+    const bool left = range.left();
+    if (lane == 0) a.redo[8 * blockIdx.x + wave] = left;
+  };
+
+  if (bd) {
+    // (b) Z_A += Y_A^T slab; (b') R_B^T += X_B^T slab; (d1) Z1 = Y_1^T slab: B = slab (K =
+    // i1, columns).  Waves 0, 1 take Z_A, its A rows from LDS; waves 2, 3 the other, whose A
+    // fragments (the same for every sub-tile of a slab) stay in registers, which leaves the
+    // LDS to two more stages of T.
+    const int iBl = 16 * (wave % NCB) + l16;
+    const bool zA_role = wave < NCB;
+    constexpr int NB = TT ? CBR : KB, NS = TT ? B2 : 1;      // row blocks, slabs with rows of their own
+    auto slab8 = [&](const float* Ms, int t, f32x4_t (&b)[2]) {
+      b[0] = *reinterpret_cast<const f32x4_t*>(&Ms[ZN::off(iBl, 32 * t + 8 * lg)]);
+      b[1] = *reinterpret_cast<const f32x4_t*>(&Ms[ZN::off(iBl, 32 * t + 8 * lg + 4)]);
+    };
+    auto split8 = [&](const f32x4_t (&b)[2]) {
+      const float x[8] = {b[0][0], b[0][1], b[0][2], b[0][3], b[1][0], b[1][1], b[1][2], b[1][3]};
+      return split3(x);
+    };
+    if (zA_role) {
+      f32x4_t zA[KB];
+      float* PZ = static_cast<float*>(a.PZA) + static_cast<int64_t>(tA) * KP * nB + c_tile + iBl;
+#pragma unroll
+      for (int s = 0; s < NST - 1; ++s) issue(s);
+      // Before the barrier of sub-tile s this wave's copies of it have to have landed.
+      // Loads and stores complete in order, and after those copies the wave issued the
+      // sixteen of s + 1 and s + 2 and the twelve stores of each column block that ended
+      // after them (a barrier keeps either from moving to another sub-tile).
+      auto copy_stage = [&](int s) {
+        if (s < 2) __builtin_amdgcn_s_waitcnt(0x4070);          // vmcnt(16) lgkmcnt(0)
+        else if (s == 2 || s % 2) __builtin_amdgcn_s_waitcnt(0x407c);   // vmcnt(28) lgkmcnt(0)
+        else __builtin_amdgcn_s_waitcnt(0x8078);                // vmcnt(40) lgkmcnt(0)
+        barrier();                          // everyone's reads of s - 1's stage are done too
+        issue(s + NST - 1);
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      static_assert(KB == 3 && NST == 4 && B2 == 2, "the counts of copy_stage");
+      for (int cb = 0; cb < a.CB; ++cb) {
+#pragma unroll
+        for (int rb = 0; rb < KB; ++rb) zA[rb] = zero;
+#pragma unroll
+        for (int i2l = 0; i2l < B2; ++i2l) {
+          copy_stage(cb * B2 + i2l);
+          const float* Ms = stage(cb * B2 + i2l);
+          const uint16_t* Ys = YRs + i2l * Lay::YROWS * N1;
+          // a step's reads go out before the previous step's products
+          f32x4_t b[2][2];
+          Bf3 y[2][KB];
+          auto load = [&](int t, int q) {
+            slab8(Ms, t, b[q]);
+#pragma unroll
+            for (int rb = 0; rb < KB; ++rb)
+#pragma unroll
+              for (int p = 0; p < 3; ++p)
+                y[q][rb].p[p] = __builtin_bit_cast(
+                    bf16x8_t, *reinterpret_cast<const u16x8_t*>(Ys + ZY::off(p * KP + 16 * rb + l16, 32 * t + 8 * lg)));
+          };
+          load(0, 0);
+#pragma unroll
+          for (int t = 0; t < NK; ++t) {
+            lds_wait_all();
+            if (t + 1 < NK) load(t + 1, (t + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mfma3(y[t & 1], split8(b[t & 1]), zA);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        // the tile's row range of Z_A for these columns
+#pragma unroll
+        for (int rb = 0; rb < KB; ++rb) {
+          range.add(zA[rb]);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) PZ[(16 * rb + 4 * lg + v) * nB + cb * SC] = zA[rb][v];
+        }
+      }
+      __builtin_amdgcn_s_waitcnt(0);        // no copy outlives the workgroup
+      mark();
+      return;
+    }
+    Bf3 y[NS][NK][NB];
+    {
+      const uint16_t* Y = TT ? a.XB3 : a.Y13;
+      const int64_t ld = TT ? nA : N1, rows = TT ? R : KP;
+#pragma unroll
+      for (int i = 0; i < NS; ++i)
+#pragma unroll
+        for (int t = 0; t < NK; ++t)
+#pragma unroll
+          for (int rb = 0; rb < NB; ++rb)
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+              y[i][t][rb].p[p] = __builtin_bit_cast(
+                  bf16x8_t, *reinterpret_cast<const u16x8_t*>(Y + (p * rows + 16 * rb + l16) * ld +
+                                                              (TT ? (i2_0 + i) * N1 : 0) + 32 * t + 8 * lg));
+    }
+    f32x4_t zB[NB];
+    float* PZ = TT ? static_cast<float*>(a.PRB) + static_cast<int64_t>(tA) * R * nB + c_tile + iBl
+                   : static_cast<float*>(a.Z1) + (i2_0 * nB + c_tile + iBl) * KP + 4 * lg;
+    for (int cb = 0; cb < a.CB; ++cb) {
+#pragma unroll
+      for (int i2l = 0; i2l < B2; ++i2l) {
+        if (!TT || i2l == 0) {
+#pragma unroll
+          for (int rb = 0; rb < NB; ++rb) zB[rb] = zero;
+        }
+        next_stage();
+        const float* Ms = stage(cb * B2 + i2l);
+        f32x4_t b[TT ? 1 : 2][2];           // TT: the registers hold X_B rows instead
+        if (!TT) slab8(Ms, 0, b[0]);
+#pragma unroll
+        for (int t = 0; t < NK; ++t) {
+          if (TT) slab8(Ms, t, b[0]);
+          lds_wait_all();
+          if (!TT && t + 1 < NK) slab8(Ms, t + 1, b[TT ? 0 : (t + 1) & 1]);
+          __builtin_amdgcn_sched_barrier(0);
+          mfma3(y[TT ? i2l : 0][t], split8(b[TT ? 0 : t & 1]), zB);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (!TT) {                // Z1 rows [i_2][i_B][j1], 64-byte pieces a lane group
+#pragma unroll
+          for (int rb = 0; rb < NB; ++rb) {
+            range.add(zB[rb]);
+            *reinterpret_cast<f32x4_t*>(PZ + (i2l * nB + cb * SC) * KP + 16 * rb) = zB[rb];
+          }
+        }
+      }
+      if constexpr (TT) {                   // the tile's row range of R_B^T for these columns
+#pragma unroll
+        for (int rb = 0; rb < NB; ++rb) {
+          range.add(zB[rb]);
+          int64_t ld = nB;                  // the rows' addresses formed here, not held through the loop
+          asm volatile("" : "+s"(ld));
+#pragma unroll
+          for (int v = 0; v < 4; ++v) PZ[(16 * rb + 4 * lg + v) * ld + cb * SC] = zB[rb][v];
+        }
+      }
+    }
+    mark();
+    return;
+  }
+
+  // (a) R_A and (c) R_1: A = slab (rows i1, K = the sub-tile's 32 columns)
+  f32x4_t rA[2][B2][CBR], r1[2][CBR];       // [i1 block][slab][column block]
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < CBR; ++c) {
+      r1[h][c] = zero;
+#pragma unroll
+      for (int i = 0; i < B2; ++i) rA[h][i][c] = zero;
+    }
+  const int i1base = 32 * (wave - 4);
+  const float *xrow[CBR], *x1row[CBR];      // X_A row j, X_1 row (j, i2_0) at the lane's first column
+#pragma unroll
+  for (int c = 0; c < CBR; ++c) {
+    const int64_t j = 16 * c + l16;
+    xrow[c] = XA + j * nB + c_tile + 8 * lg;
+    x1row[c] = X1 + (j * n2 + i2_0) * nB + c_tile + 8 * lg;
+  }
+  float xa[CBR][8], x1[B2][CBR][8];         // the next column block's X values of the lane
+  auto load_x = [&](const float* const (&row)[CBR], int64_t off, float (&x)[CBR][8]) {
+#pragma unroll
+    for (int c = 0; c < CBR; ++c) {
+      const f32x4_t u = *reinterpret_cast<const f32x4_t*>(row[c] + off);
+      const f32x4_t v = *reinterpret_cast<const f32x4_t*>(row[c] + off + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[c][e] = u[e];
+        x[c][e + 4] = v[e];
+      }
+    }
+  };
+  load_x(xrow, 0, xa);
+#pragma unroll
+  for (int i = 0; i < B2; ++i) load_x(x1row, i * nB, x1[i]);
+  Bf3 xas[CBR];
+  for (int cb = 0; cb < a.CB; ++cb) {
+    const int64_t next = static_cast<int64_t>(cb + 1 < a.CB ? cb + 1 : cb) * SC;
+#pragma unroll
+    for (int i2l = 0; i2l < B2; ++i2l) {
+      next_stage();
+      const float* Ms = stage(cb * B2 + i2l);
+      // The BF16 MFMA rounds its sums down, not to nearest, which adds up over thousands of
+      // columns.  So a sub-tile's sums start from zero and are added to the tile's with
+      // rounding to nearest, and every second sub-tile of a sum is formed negated, where down
+      // is the other way: R_1 of a 128^4 tensor is 3e-7 off its FP64 value (6.7e-6 in one
+      // chain, 1.6e-6 without the negation and on the FP32 MFMA).
+      const float sign = (cb + i2l) % 2 ? -1.f : 1.f;
+      float v[2][8];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[h][e] = sign * Ms[ZN::off(8 * lg + e, i1base + 16 * h + l16)];
+      Bf3 x1s[CBR];
+#pragma unroll
+      for (int c = 0; c < CBR; ++c) {
+        if (i2l == 0) xas[c] = split3(xa[c]);
+        x1s[c] = split3(x1[i2l][c]);
+      }
+      if (i2l == 0) load_x(xrow, next, xa);
+      load_x(x1row, i2l * nB + next, x1[i2l]);
+      const Bf3 as[2] = {split3(v[0]), split3(v[1])};
+#pragma unroll
+      for (int c = 0; c < CBR; ++c) {
+        f32x4_t t[2] = {zero, zero}, u[2] = {zero, zero};
+        mfma3(as, xas[c], t);
+        mfma3(as, x1s[c], u);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            rA[h][i2l][c][e] = __builtin_fmaf(sign, t[h][e], rA[h][i2l][c][e]);
+            r1[h][c][e] = __builtin_fmaf(sign, u[h][e], r1[h][c][e]);
+          }
+      }
+    }
+  }
+  float* PRA = static_cast<float*>(a.PRA);
+  float* PR1 = static_cast<float*>(a.PR1);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < CBR; ++c) {
+      range.add(r1[h][c]);
+#pragma unroll
+      for (int i = 0; i < B2; ++i) range.add(rA[h][i][c]);
+    }
+  mark();
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < CBR; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i1 = i1base + 16 * h + 4 * lg + v, j = 16 * c + l16;
+#pragma unroll
+        for (int i = 0; i < B2; ++i)
+          PRA[(static_cast<int64_t>(tB) * nA + (i2_0 + i) * N1 + i1) * R + j] = rA[h][i][c][v];
+        PR1[((static_cast<int64_t>(tA) * a.TB + tB) * N1 + i1) * R + j] = r1[h][c][v];
+      }
+}
+
 // sum_{t < n} p[t * stride] in FP64 with eight interleaved partial sums (t mod 8),
 // combined in a fixed order: eight loads in flight per thread.
 template <typename Acc>
@@ -836,6 +1256,24 @@ __global__ void gather_copy(const double* src, TO* out, int64_t d0, int64_t d1, 
   }
 }
 
+// The same copy split into the BF16 planes of split3: out[p][o], p = h, m, l.
+__global__ void gather_split(const double* src, uint16_t* out, int64_t d0, int64_t d1, int64_t s0, int64_t s1,
+                             int64_t lim) {
+  const int64_t total = d0 * d1;
+  for (int64_t o = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; o < total;
+       o += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+    const int64_t i0 = o % d0, i1 = o / d0;
+    float v = i1 < lim ? static_cast<float>(src[i0 * s0 + i1 * s1]) : 0.0f;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const uint32_t b = __float_as_uint(v);
+      const uint16_t q = static_cast<uint16_t>((b + 0x7FFFu + ((b >> 16) & 1u)) >> 16);
+      out[p * total + o] = q;
+      v -= bf16_bits_to_f32(q);
+    }
+  }
+}
+
 }  // namespace
 
 void copy_layout(const double* src, void* out, int dt, int64_t d0, int64_t d1, int64_t d2, int64_t s0, int64_t s1,
@@ -888,7 +1326,13 @@ void launch_sttnn(bool tt, bool zout, const SttnnArgs& a, hipStream_t st) {
   constexpr int SC = sc_of<DT>(), SCZ = sc_of<DT, R, true>();
   constexpr int B2T = b2_of<DT, R, true>(), B2S = b2_of<DT, R, false>(), B2Z = b2_of<DT, R, false, true>();
   const dim3 grid(a.TA * a.TB);
-  if (tt) hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2T, SC, true, false>), grid, dim3(kThreadsF), 0, st, a);
+  if constexpr (split_form(DT, R, true, false)) {
+    static_assert(B2T == X3Layout::B2 && B2Z == X3Layout::B2 && SC == X3Layout::SC && KP == X3Layout::KP,
+                  "one tile shape");
+    if (tt) hipLaunchKernelGGL(sttnn_t4_x3_kernel<true>, grid, dim3(kThreadsF), 0, st, a);
+    else if (zout) hipLaunchKernelGGL(sttnn_t4_x3_kernel<false>, grid, dim3(kThreadsF), 0, st, a);
+  }
+if (tt) hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2T, SC, true, false>), grid, dim3(kThreadsF), 0, st, a);
   else if (zout) hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2Z, SCZ, false, true>), grid, dim3(kThreadsF), 0, st, a);
   else hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2S, SC, false, false>), grid, dim3(kThreadsF), 0, st, a);
 }
@@ -983,11 +1427,18 @@ void fused_prepare(Plan& P, hipStream_t st) {
 
   const int dt = P.dtype;
   const int64_t es = elem_size(dt);
+  const bool x3 = split_form(dt, R, tt, zout);            // Y_A, Y_1, X_B as three BF16 planes as well
   // DRM copies in the fragment layouts of the kernel (the FP64 arrays of a lower-precision
   // plan hold the rounded values already, so these copies are exact)
   F.XA = P.alloc(es * nB * R);
   F.X1 = P.alloc(es * nAs / N1 * nB * R);
   F.YA = P.alloc(es * nAs * KP);
+  if (x3) {
+    F.YA3 = P.alloc(6 * nAs * KP);
+    if (tt) F.XB3 = P.alloc(6 * nAs * R);
+    else F.Y13 = P.alloc(6 * static_cast<int64_t>(N1) * KP);
+    F.redo = P.alloc(4 * int64_t(8) * TA * TB);
+  }
   const int x2dt = zout ? zdt : dt;
   if (tt) {
     F.XB = P.alloc(es * nAs * R);
@@ -1002,11 +1453,18 @@ void fused_prepare(Plan& P, hipStream_t st) {
   if (!P.dry) {
     copy_layout(NA.X64, F.XA, dt, nB, R, 1, R, 1, 0, 0, nB, st);                     // [j][iB]
     copy_layout(L1.X64, F.X1, dt, nB, n2, R, n2 * R, R, 1, 0, nB, st);               // [j][i2][iB]
-    copy_layout(NA.Y64, F.YA, dt, nAs, KP, 1, k, 1, 0, 1, k, st);                    // [jA][iA]
+    auto rows = [&](const double* src, void* out, void* out3, int64_t d0, int64_t d1, int64_t s0) {   // [j][i]
+      copy_layout(src, out, dt, d0, d1, 1, s0, 1, 0, 1, s0, st);
+      if (!x3) return;
+      const int blocks = static_cast<int>(std::min<int64_t>((d0 * d1 + 255) / 256, 16384));
+      hipLaunchKernelGGL(gather_split, dim3(blocks), dim3(256), 0, st, src, static_cast<uint16_t*>(out3), d0, d1, s0,
+                         int64_t(1), s0);
+    };
+    rows(NA.Y64, F.YA, F.YA3, nAs, KP, k);                                           // [jA][iA]
     if (tt) {
-      copy_layout(XB64, F.XB, dt, nAs, R, 1, R, 1, 0, 1, R, st);                     // [j][iA]
+      rows(XB64, F.XB, F.XB3, nAs, R, R);                                            // [j][iA]
     } else {
-      copy_layout(L1.Y64, F.Y1, dt, N1, KP, 1, k, 1, 0, 1, k, st);                   // [j1][i1]
+      rows(L1.Y64, F.Y1, F.Y13, N1, KP, k);                                          // [j1][i1]
       copy_layout(L2.X64, F.X2, x2dt, KP, nB, R, R, static_cast<int64_t>(k) * R, 1, 0, k, st);  // [j][iB][j1]
     }
   }
@@ -1047,6 +1505,10 @@ bool try_fused_update(Plan& P, const void* block, const int64_t* off, const int6
   a.PR2 = F.PR2;
   a.PRB = F.PRB;
   a.Z1 = F.Z1;
+  a.YA3 = static_cast<const uint16_t*>(F.YA3);
+  a.Y13 = static_cast<const uint16_t*>(F.Y13);
+  a.XB3 = static_cast<const uint16_t*>(F.XB3);
+  a.redo = static_cast<uint32_t*>(F.redo);
   if (P.dtype == TTNN_BF16) launch_sttnn_dt<TTNN_BF16>(F.R, F.tt, F.zout, a, st);
   else if (P.dtype == TTNN_F32) launch_sttnn_dt<TTNN_F32>(F.R, F.tt, F.zout, a, st);
   else launch_sttnn_dt<TTNN_F64>(F.R, F.tt, F.zout, a, st);

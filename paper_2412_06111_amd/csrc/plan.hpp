@@ -57,6 +57,7 @@ struct FusedT4 {
   void* Z1 = nullptr;
   void *XA = nullptr, *X1 = nullptr, *YA = nullptr, *Y1 = nullptr, *X2 = nullptr, *XB = nullptr;
   void *PRA = nullptr, *PZA = nullptr, *PR1 = nullptr, *PR2 = nullptr, *PRB = nullptr;
+  void *YA3 = nullptr, *Y13 = nullptr, *XB3 = nullptr, *redo = nullptr;   // FP32, r = 32: split operands, tile marks
 };
 
 struct Plan {
