@@ -237,6 +237,34 @@ __device__ inline void bd_chain(const typename P::T* Ms, int iBl, int lg, LoadA&
   }
 }
 
+// A barrier without the fence of __syncthreads, which would wait for every copy in flight:
+// the waits before it are the caller's, and no access moves across it.
+__device__ __forceinline__ void raw_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Tile of this workgroup.  Workgroups are dealt to the eight XCDs round robin; each XCD
+// takes a range of slab groups across every column band when TA allows, so the tiles that
+// share an L2 run through the same slabs in step and fetch each Y_A row once between them
+// (X_A, the smaller operand, is then shared by fewer tiles).
+__device__ __forceinline__ void tile_of(const SttnnArgs& a, int& tA, int& tB) {
+  const int w = blockIdx.x;
+  if (a.TA % 8 == 0) {
+    const int x = w % 8, j = w / 8, gpx = a.TA / 8;
+    tA = x * gpx + j % gpx;
+    tB = j / gpx;
+  } else if (a.TB % 8 == 0) {
+    const int x = w % 8, j = w / 8, bpx = a.TB / 8;
+    tB = x * bpx + j / a.TA;
+    tA = j % a.TA;
+  } else {
+    tB = w / a.TA;
+    tA = w % a.TA;
+  }
+}
+
 // The FP32 forms at r = 32 whose products are split into BF16 ones (sttnn_t4_x3_kernel).
 constexpr bool split_form(int dt, int R, bool tt, bool zout) { return dt == TTNN_F32 && R == 32 && (tt || zout); }
 
@@ -296,26 +324,8 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_kernel(SttnnArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
 
-  // tile of this workgroup.  Workgroups are dealt to the eight XCDs round robin; each
-  // XCD takes a range of slab groups across every column band when TA allows, so the
-  // tiles that share an L2 run through the same slabs in step and fetch each Y_A row
-  // once between them (X_A, the smaller operand, is then shared by fewer tiles).
   int tA, tB;
-  {
-    const int w = blockIdx.x;
-    if (a.TA % 8 == 0) {
-      const int x = w % 8, j = w / 8, gpx = a.TA / 8;
-      tA = x * gpx + j % gpx;
-      tB = j / gpx;
-    } else if (a.TB % 8 == 0) {
-      const int x = w % 8, j = w / 8, bpx = a.TB / 8;
-      tB = x * bpx + j / a.TA;
-      tA = j % a.TA;
-    } else {
-      tB = w / a.TA;
-      tA = w % a.TA;
-    }
-  }
+  tile_of(a, tA, tB);
   const int64_t i2_0 = static_cast<int64_t>(tA) * B2;
   const int64_t c_tile = static_cast<int64_t>(tB) * a.CB * SC;
   const T* XA = static_cast<const T*>(a.XA);
@@ -821,22 +831,8 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  int tA, tB;                               // as in sttnn_t4_kernel
-  {
-    const int w = blockIdx.x;
-    if (a.TA % 8 == 0) {
-      const int x = w % 8, j = w / 8, gpx = a.TA / 8;
-      tA = x * gpx + j % gpx;
-      tB = j / gpx;
-    } else if (a.TB % 8 == 0) {
-      const int x = w % 8, j = w / 8, bpx = a.TB / 8;
-      tB = x * bpx + j / a.TA;
-      tA = j % a.TA;
-    } else {
-      tB = w / a.TA;
-      tA = w % a.TA;
-    }
-  }
+  int tA, tB;
+  tile_of(a, tA, tB);
   const int64_t i2_0 = static_cast<int64_t>(tA) * B2;
   const int64_t c_tile = static_cast<int64_t>(tB) * a.CB * SC;
   const int64_t nA = a.nA, nB = a.nB, n2 = a.n2;
@@ -869,16 +865,9 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
   __syncthreads();                          // the resident rows are there
 
   static_assert(B2 == 2, "the loops' slabs");
-  // A barrier without the fence of __syncthreads, which would wait for every copy in flight;
-  // the LDS reads before it are waited for, and no access moves across it.
-  auto barrier = [&]() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
   auto next_stage = [&]() {
     lds_wait_all();                         // this wave's reads of the last stage are done
-    barrier();
+    raw_barrier();
   };
   // The roles run loops of their own, so that neither's registers are held through the
   // other's code; both pass one barrier a sub-tile.
@@ -918,7 +907,7 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
         if (s < 2) __builtin_amdgcn_s_waitcnt(0x4070);          // vmcnt(16) lgkmcnt(0)
         else if (s == 2 || s % 2) __builtin_amdgcn_s_waitcnt(0x407c);   // vmcnt(28) lgkmcnt(0)
         else __builtin_amdgcn_s_waitcnt(0x8078);                // vmcnt(40) lgkmcnt(0)
-        barrier();                          // everyone's reads of s - 1's stage are done too
+        raw_barrier();                      // everyone's reads of s - 1's stage are done too
         issue(s + NST - 1);
         __builtin_amdgcn_sched_barrier(0);
       };
@@ -1128,6 +1117,237 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
       }
 }
 
+// ---------------------------------------------------------------- FP64 Z1-out at r = 32
+// Bound by the FP64 MFMA: 85.9 GFLOP for a 128^4 tensor, 1193 us at the 72 TFLOP/s that a
+// large product reaches.  A sub-tile (one slab, 32 columns) is 640 MFMAs, 160 a SIMD: waves
+// 0, 1 take Z_A and waves 2, 3 Z1 for 16 columns each (96), waves 4-7 R_A and R_1 for 32
+// rows of i1 each (64), so that the two waves of a SIMD have the same work on every SIMD
+// and one barrier a sub-tile is all that holds them together.  For that the operands that
+// every sub-tile reads stay where they are used: the Y_A rows of the tile's two slabs in LDS
+// (96 KB, beside two 32 KB stages of T), Y_1 in the registers of waves 2, 3 (192 a lane).
+// X_A and X_1 go from global memory to the registers of waves 4-7, each value right after its
+// last product for its next use, a sub-tile on.  Waves 0, 1, which load nothing else, copy
+// the slab a sub-tile ahead.
+// 128^4, r = 32: the sweep 2450 -> 1495 us in sttnn_t4_kernel's place (one phase for (b)/(d1)
+// and one for (a)/(c), the matrix cores 47% busy; now 85%, at the 2.07 GHz that the card
+// holds there), the whole step with the FP64 tail 2902 -> 1910 us.  Two slabs a tile in place
+// of four double the partials of Z_A: their reduction takes 116 us where it took 63.
+typedef double f64x2_t __attribute__((ext_vector_type(2)));
+
+struct F64Layout {
+  static constexpr int R = 32, KP = 48, B2 = 2, SC = 32, NST = 2;
+  static constexpr size_t MS = size_t(SC) * N1 * 8;           // one stage of T
+  static constexpr size_t OFF_YR = NST * MS;
+  static constexpr size_t TOTAL = OFF_YR + size_t(B2) * KP * N1 * 8;
+  static_assert(TOTAL <= 160 * 1024, "LDS");
+};
+
+__global__ __launch_bounds__(kThreadsF) void sttnn_t4_f64_kernel(SttnnArgs a) {
+  using Lay = F64Layout;
+  using P = Pol<TTNN_F64>;
+  constexpr int R = Lay::R, KP = Lay::KP, B2 = Lay::B2, SC = Lay::SC;
+  constexpr int CBR = R / 16, KB = KP / 16, NCB = SC / 16, NT = N1 / 8;
+  using Z = Swz<double, N1>;
+  __shared__ __align__(16) char smem[Lay::TOTAL];
+  double* YRs = reinterpret_cast<double*>(smem + Lay::OFF_YR);
+
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tA, tB;
+  tile_of(a, tA, tB);
+  const int64_t i2_0 = static_cast<int64_t>(tA) * B2;
+  const int64_t c_tile = static_cast<int64_t>(tB) * a.CB * SC;
+  const int64_t nA = a.nA, nB = a.nB, n2 = a.n2;
+  const int nsub = a.CB * B2;
+  static_assert(B2 == 2 && NCB == 2 && CBR == 2 && Lay::NST == 2 && Z::CPR == 64, "the loops' slabs and roles");
+  const f64x4_t zero = {0.0, 0.0, 0.0, 0.0};
+
+  auto stage = [&](int s) { return reinterpret_cast<double*>(smem + (s % 2) * Lay::MS); };
+#pragma unroll
+  for (int i = 0; i < B2; ++i)
+    lds_dma_rows<double, N1>(static_cast<const double*>(a.YA) + (i2_0 + i) * N1, nA, YRs + i * KP * N1, KP, wave, lane);
+  __syncthreads();                          // the resident rows are there
+  auto next_stage = [&]() {
+    lds_wait_all();                         // this wave's reads of the last stage are done
+    raw_barrier();
+  };
+
+  if (wave < 4) {
+    const int iBl = 16 * (wave % NCB) + l16;
+    // a step is eight values of i1: 2 lg, 2 lg + 1 of the lane, in two products
+    auto pair = [&](const double* row0, int r, int t) {
+      return *reinterpret_cast<const f64x2_t*>(&row0[Z::off(r, 8 * t + 2 * lg)]);
+    };
+    if (wave < NCB) {
+      const double* T = static_cast<const double*>(a.T);
+      // sixteen rows a wave of the slab's copy of sub-tile s (none past the last)
+      auto issue = [&](int s) {
+        if (s >= nsub) return;
+        const double* g = T + (i2_0 + s % B2) * N1 + nA * (c_tile + static_cast<int64_t>(s / B2) * SC);
+        double* l = stage(s);
+#pragma unroll
+        for (int u = 0; u < SC / 2; ++u) {
+          const int r = 2 * u + wave;
+          lds_dma16(g + r * nA + (lane ^ (r & Z::MASK)) * Z::EV, l + r * N1);
+        }
+      };
+      f64x4_t zA[KB];
+      double* PZ = static_cast<double*>(a.PZA) + static_cast<int64_t>(tA) * KP * nB + c_tile + iBl;
+      issue(0);
+      for (int cb = 0; cb < a.CB; ++cb) {
+#pragma unroll
+        for (int rb = 0; rb < KB; ++rb) zA[rb] = zero;
+#pragma unroll
+        for (int i2l = 0; i2l < B2; ++i2l) {
+          // The copies of this sub-tile have to have landed.  Loads and stores complete in
+          // order, and after those copies, issued a sub-tile ago, come the twelve stores of
+          // the last column block if one has just ended.
+          if (i2l == 0 && cb > 0) __builtin_amdgcn_s_waitcnt(0x007c);   // vmcnt(12) lgkmcnt(0)
+          else __builtin_amdgcn_s_waitcnt(0x0070);                      // vmcnt(0) lgkmcnt(0)
+          raw_barrier();
+          issue(cb * B2 + i2l + 1);         // everyone's reads of that stage are done
+          __builtin_amdgcn_sched_barrier(0);
+          const double* Ms = stage(cb * B2 + i2l);
+          const double* Ys = YRs + i2l * KP * N1;
+          f64x2_t b[2], y[2][KB];
+          auto load = [&](int t, int q) {
+            b[q] = pair(Ms, iBl, t);
+#pragma unroll
+            for (int rb = 0; rb < KB; ++rb) y[q][rb] = pair(Ys, 16 * rb + l16, t);
+          };
+          load(0, 0);
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            lds_wait_all();
+            if (t + 1 < NT) load(t + 1, (t + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+              for (int rb = 0; rb < KB; ++rb) zA[rb] = P::mfma(y[t & 1][rb][v], b[t & 1][v], zA[rb]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+#pragma unroll
+        for (int rb = 0; rb < KB; ++rb)     // the tile's row range of Z_A for these columns
+#pragma unroll
+          for (int v = 0; v < 4; ++v) PZ[(16 * rb + P::crow(lane, v)) * nB + cb * SC] = zA[rb][v];
+      }
+      return;
+    }
+    // Z1: Y_1's rows dealt so that a lane's four results of a block are neighbours
+    f64x2_t y[NT][KB];
+    const double* Y1 = static_cast<const double*>(a.Y1) + (4 * (l16 % 4) + l16 / 4) * N1 + 2 * lg;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int rb = 0; rb < KB; ++rb) y[t][rb] = *reinterpret_cast<const f64x2_t*>(Y1 + 16 * rb * N1 + 8 * t);
+    double* PZ = static_cast<double*>(a.Z1) + (i2_0 * nB + c_tile + iBl) * KP + 4 * lg;
+    for (int s = 0; s < nsub; ++s) {
+      f64x4_t z1[KB];
+#pragma unroll
+      for (int rb = 0; rb < KB; ++rb) z1[rb] = zero;
+      next_stage();
+      const double* Ms = stage(s);
+      f64x2_t b[2];
+      b[0] = pair(Ms, iBl, 0);
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        lds_wait_all();
+        if (t + 1 < NT) b[(t + 1) & 1] = pair(Ms, iBl, t + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+          for (int rb = 0; rb < KB; ++rb) z1[rb] = P::mfma(y[t][rb][v], b[t & 1][v], z1[rb]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      double* o = PZ + ((s % B2) * nB + (s / B2) * SC) * KP;
+#pragma unroll
+      for (int rb = 0; rb < KB; ++rb) *reinterpret_cast<f64x4_t*>(o + 16 * rb) = z1[rb];
+    }
+    return;
+  }
+
+  // R_A and R_1: A = slab (rows i1, K = the sub-tile's columns, 8 lg + e of the lane)
+  f64x4_t rA[2][B2][CBR], r1[2][CBR];       // [i1 block][slab][column block]
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < CBR; ++c) {
+      r1[h][c] = zero;
+#pragma unroll
+      for (int i = 0; i < B2; ++i) rA[h][i][c] = zero;
+    }
+  const int i1base = 32 * (wave - 4);
+  // X_A row j = l16, X_1 row (j, i2_0), at the lane's first column; 16 rows on the next block
+  const double* XA = static_cast<const double*>(a.XA) + l16 * nB + c_tile + 8 * lg;
+  const double* X1 = static_cast<const double*>(a.X1) + (l16 * n2 + i2_0) * nB + c_tile + 8 * lg;
+  const int64_t ca = 16 * nB, c1 = 16 * n2 * nB;
+  f64x2_t xa[4][CBR], x1[4][CBR];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int c = 0; c < CBR; ++c) {
+      xa[q][c] = *reinterpret_cast<const f64x2_t*>(XA + c * ca + 2 * q);
+      x1[q][c] = *reinterpret_cast<const f64x2_t*>(X1 + c * c1 + 2 * q);
+    }
+  for (int cb = 0; cb < a.CB; ++cb) {
+    const int64_t next = static_cast<int64_t>(cb + 1 < a.CB ? cb + 1 : cb) * SC;
+#pragma unroll
+    for (int i2l = 0; i2l < B2; ++i2l) {
+      next_stage();
+      const double* Ms = stage(cb * B2 + i2l);
+      double v[2][8];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[h][e] = Ms[Z::off(8 * lg + e, i1base + 16 * h + l16)];
+      const double* x1n = X1 + (i2l == 0 ? nB + static_cast<int64_t>(cb) * SC : next);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int c = 0; c < CBR; ++c)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) rA[h][i2l][c] = P::mfma(v[h][2 * q + u], xa[q][c][u], rA[h][i2l][c]);
+        if (i2l == B2 - 1) {
+#pragma unroll
+          for (int c = 0; c < CBR; ++c) xa[q][c] = *reinterpret_cast<const f64x2_t*>(XA + c * ca + next + 2 * q);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int c = 0; c < CBR; ++c)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) r1[h][c] = P::mfma(v[h][2 * q + u], x1[q][c][u], r1[h][c]);
+#pragma unroll
+        for (int c = 0; c < CBR; ++c) x1[q][c] = *reinterpret_cast<const f64x2_t*>(x1n + c * c1 + 2 * q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  double* PRA = static_cast<double*>(a.PRA);
+  double* PR1 = static_cast<double*>(a.PR1);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < CBR; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i1 = i1base + 16 * h + P::crow(lane, v), j = 16 * c + l16;
+#pragma unroll
+        for (int i = 0; i < B2; ++i)
+          PRA[(static_cast<int64_t>(tB) * nA + (i2_0 + i) * N1 + i1) * R + j] = rA[h][i][c][v];
+        PR1[((static_cast<int64_t>(tA) * a.TB + tB) * N1 + i1) * R + j] = r1[h][c][v];
+      }
+}
+
 // sum_{t < n} p[t * stride] in FP64 with eight interleaved partial sums (t mod 8),
 // combined in a fixed order: eight loads in flight per thread.
 template <typename Acc>
@@ -1299,13 +1519,13 @@ struct Shape {
 
 // Tile shape per dtype: B2 slabs of i_2 per tile, SC columns per sub-tile (sized so
 // that the slab, the DRM rows of a sub-tile and the Z1 stash fit the LDS budget).
-// The FP32 Z1-out and TTNN forms at r = 32 take two slabs, so that their Y_A (and X_B)
-// rows stay in LDS.
+// The FP32 Z1-out and TTNN forms and the FP64 Z1-out form at r = 32 take two slabs, so that
+// their Y_A (and X_B) rows stay in LDS.
 template <int DT, int R, bool TT, bool ZO = false>
 constexpr int b2_of() {
   return DT == TTNN_BF16 ? (R >= 64 ? 2 : (ZO || TT) && R == 32 ? 4 : 8)
          : DT == TTNN_F32 ? (R >= 64 || ((ZO || TT) && R == 32) ? 2 : 4)
-                          : (R >= 64 || TT ? 2 : 4);
+                          : (R >= 64 || TT || (ZO && R == 32) ? 2 : 4);
 }
 // BF16 Z1-out at r = 64 takes 32-column sub-tiles: with them the FP32 Z1 stash, the
 // resident Y_A rows of both slabs and staged X_A / X_1 rows fit the LDS (at 64 columns
@@ -1318,7 +1538,7 @@ constexpr int sc_of() {
 Shape shape_for(int dt, int R, bool tt, bool zout) {
   if (dt == TTNN_BF16) return {R >= 64 ? 2 : (zout || tt) && R == 32 ? 4 : 8, zout && !tt && R >= 64 ? 32 : 64};
   if (dt == TTNN_F32) return {R >= 64 || ((zout || tt) && R == 32) ? 2 : 4, 32};
-  return {R >= 64 || tt ? 2 : 4, 32};
+  return {R >= 64 || tt || (zout && R == 32) ? 2 : 4, 32};
 }
 
 template <int DT, int R, int KP>
@@ -1332,8 +1552,12 @@ void launch_sttnn(bool tt, bool zout, const SttnnArgs& a, hipStream_t st) {
     if (tt) hipLaunchKernelGGL(sttnn_t4_x3_kernel<true>, grid, dim3(kThreadsF), 0, st, a);
     else if (zout) hipLaunchKernelGGL(sttnn_t4_x3_kernel<false>, grid, dim3(kThreadsF), 0, st, a);
   }
-if (tt) hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2T, SC, true, false>), grid, dim3(kThreadsF), 0, st, a);
-  else if (zout) hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2Z, SCZ, false, true>), grid, dim3(kThreadsF), 0, st, a);
+  if (tt) hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2T, SC, true, false>), grid, dim3(kThreadsF), 0, st, a);
+  else if (zout && DT == TTNN_F64 && R == 32) hipLaunchKernelGGL(sttnn_t4_f64_kernel, grid, dim3(kThreadsF), 0, st, a);
+  else if (zout) {
+    if constexpr (DT != TTNN_F64 || R != 32)
+      hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2Z, SCZ, false, true>), grid, dim3(kThreadsF), 0, st, a);
+  }
   else hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2S, SC, false, false>), grid, dim3(kThreadsF), 0, st, a);
 }
 

@@ -1,0 +1,28 @@
+"""The role-split sweeps at r = 32 (FP64 Z1-out, FP32 Z1-out and TTNN), two slabs and 32
+columns a sub-tile, at the edges of their range: one slab pair, an odd number of pairs, one
+column block a tile, several tiles a column band, Y rows short of the padded 48."""
+import numpy as np
+import pytest
+
+import oracle as O
+from gpu_util import TOL_ARITH, failures, sketch_errors, to_device
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(128, 2, 16, 64), (128, 6, 8, 32), (128, 10, 24, 24), (128, 34, 16, 64)]
+
+
+@pytest.mark.parametrize("dims", SHAPES, ids=str)
+@pytest.mark.parametrize("p", [1, 16])
+@pytest.mark.parametrize("variant,dtype", [("sttnn", "f64"), ("sttnn", "f32"), ("ttnn", "f32")])
+def test_role_split_sweep_edges(dims, p, variant, dtype):
+    import paper_2412_06111_amd as P
+    T = np.random.default_rng(21).standard_normal(dims)
+    dev, consumed = to_device(T, dtype)
+    plan = P.Plan(O.T4, dims, 32, p, variant=variant, dtype=dtype, seed=9)
+    plan.update(dev, alpha=0.5)
+    plan.update(dev, alpha=0.5)
+    tree = O.Tree(O.T4, dims, 32, p)
+    sk = O.sketch(consumed, tree, O.DRMs(tree, 9, variant, dtype), variant)
+    bad = failures(sketch_errors(plan, tree, sk), TOL_ARITH[dtype])
+    assert not bad, bad
