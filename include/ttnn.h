@@ -34,11 +34,7 @@
  *    done on the host before anything is enqueued and are reported synchronously.
  *    A failed HIP call makes the plan's status sticky (TTNN_E_HIP): later calls on
  *    that plan return it until ttnn_reset.  Input buffers must stay valid until
- *    the stream has passed the call.  A whole-tensor update may run part of its
- *    work on a side stream that the plan owns (default priority); that work starts
- *    after everything enqueued before the call on `stream` and is joined back into
- *    `stream` before the call returns, so ordering on `stream` is as if all of it
- *    ran there.
+ *    the stream has passed the call.
  *  - Ownership: the caller owns every buffer it passes.  A plan made by ttnn_plan
  *    lives in a device workspace the caller owns (ttnn_workspace_bytes gives its
  *    size): every device array of the plan (DRMs, FP64 accumulators, scratch) is a

@@ -671,7 +671,6 @@ void update_box_impl(Plan& P, const void* block, const int64_t* off, const int64
         a.sDc = 1;
         a.ncols = g.k;
         a.amap = box_rows(P, g.first, g.last, off, ext);
-        join_side(P, st);                       // shares the partial scratch
         if (before.empty() && whole && L == 1 && g.Yt) {
           // raw tensor, group at mode 1: Z[j + k q] = sum_i T[i + n q] Y[i][j] is the
           // MFMA right form with the contraction (i) contiguous and q as the row.  Its
@@ -728,7 +727,6 @@ void update_box_impl(Plan& P, const void* block, const int64_t* off, const int64
     a.sDc = 1;
     a.ncols = g.k;
     a.amap = box_rows(P, g.first, g.last, off, ext);
-    join_side(P, st);
     left_op(P, a, P.psi_root, 1, alpha, st);
   };
   do_root();
@@ -746,7 +744,6 @@ void update_box_impl(Plan& P, const void* block, const int64_t* off, const int64
     if (!pre.empty() && whole && t.Xt64 && right_mfma_eligible(L, n, Q, t.r, TTNN_F64)) {
       // FP64 intermediate, contraction contiguous: MFMA right form
       batch.flush();
-      join_side(P, st);
       const int nch = launch_right_mfma(in, TTNN_F64, L, n, Q, t.Xt64, t.m, t.r, P.partial, P.partial_elems, st);
       launch_reduce(P.partial, nch, n, t.r, 0, alpha, box_rows(P, t.first, t.last, off, ext), t.n, t.R, 1, 1, st);
       continue;
@@ -757,7 +754,6 @@ void update_box_impl(Plan& P, const void* block, const int64_t* off, const int64
       continue;
     }
     batch.flush();
-    join_side(P, st);
     if (pre.empty() && whole && t.Xt) {          // raw tensor, contiguous contraction: MFMA
       const int nch = launch_right_mfma(block, cd, L, n, Q, t.Xt, t.m, t.r, P.partial, P.partial_elems, st);
       launch_reduce(P.partial, nch, n, t.r, 0, alpha, box_rows(P, t.first, t.last, off, ext), t.n, t.R, 1, 1, st);
@@ -796,7 +792,6 @@ void update_box_impl(Plan& P, const void* block, const int64_t* off, const int64
   }
 
   batch.flush();
-  join_side(P, st);
 }
 }  // namespace
 

@@ -1572,25 +1572,6 @@ int64_t elem_size(int dt) { return dt == TTNN_F64 ? 8 : dt == TTNN_F32 ? 4 : 2; 
 
 }  // namespace
 
-// ---------------------------------------------------------------- side stream
-void fork_side(Plan& P, hipStream_t st, hipEvent_t after) {
-  if (!P.side) {
-    TTNN_HIP(hipStreamCreateWithFlags(&P.side, hipStreamNonBlocking));
-    for (hipEvent_t& e : P.side_ev) TTNN_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-  }
-  if (!after) {
-    TTNN_HIP(hipEventRecord(P.side_ev[0], st));
-    after = P.side_ev[0];
-  }
-  TTNN_HIP(hipStreamWaitEvent(P.side, after, 0));
-}
-
-void join_side(Plan& P, hipStream_t st) {
-  if (!P.side_pending) return;
-  TTNN_HIP(hipStreamWaitEvent(st, P.side_ev[1], 0));
-  P.side_pending = false;
-}
-
 // ---------------------------------------------------------------- plan-time setup
 void fused_prepare(Plan& P, hipStream_t st) {
   FusedT4& F = P.fused;
@@ -1742,22 +1723,17 @@ bool try_fused_update(Plan& P, const void* block, const int64_t* off, const int6
   }
 
   if (F.zout) {
-    // R_2 += alpha Z1 X_2: Z1 [i_2][(i_B, j1)] against X_2 [j][(i_B, j1)], one pass over
-    // both.  It needs only Z1 and X_2, so it runs on the plan's side stream beside the
-    // partial reduction and the FP64 jobs that follow on the caller's stream (it uses the
-    // partial scratch; the update joins it before any other user of that scratch).
-    // Every kernel of this stretch streams from HBM or waits on it, so the overlap gains
-    // little at FP32 (the kernels slow each other down); at BF16, where Z1 is half the
-    // size, it does.
-    fork_side(P, st, P.timing ? P.sweep_ev[1] : nullptr);   // the sweep's end event, when timed
+    // R_2 += alpha Z1 X_2: Z1 [i_2][(i_B, j1)] against X_2 [j][(i_B, j1)], one pass over both
+    // on the caller's stream.  Beside the reduction and the FP64 jobs that follow, on a stream
+    // of its own, every one of them took longer than alone (R_2 of a 128^4 tensor at FP32, r =
+    // 32, 220 us for 134, the reduction 83 for 48, the FP64 jobs 120 for 32), and the update
+    // 797 us for 774 (BF16 at r = 64: 1120 for 1112, FP64: 1895 for 1809).
     const int64_t K = static_cast<int64_t>(F.KP) * F.nB;
     const int zdt = P.dtype == TTNN_BF16 ? TTNN_F32 : P.dtype;      // Z1 and this X_2 copy
-    const int nch = launch_right_mfma(F.Z1, zdt, K, F.n2, 1, F.X2, K, F.R, P.partial, P.partial_elems, P.side);
+    const int nch = launch_right_mfma(F.Z1, zdt, K, F.n2, 1, F.X2, K, F.R, P.partial, P.partial_elems, st);
     const Node& n2d = P.nodes[F.node_2];
     launch_reduce(P.partial, nch, F.n2, F.R, 0, alpha, box_rows(P, n2d.first, n2d.last, off, ext), n2d.n, n2d.R, 1, 1,
-                  P.side);
-    TTNN_HIP(hipEventRecord(P.side_ev[1], P.side));
-    P.side_pending = true;
+                  st);
   }
 
   const std::vector<int> pre{F.node_A};

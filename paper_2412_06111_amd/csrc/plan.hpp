@@ -114,11 +114,6 @@ struct Plan {
   bool timing = false;
   hipEvent_t sweep_ev[2] = {nullptr, nullptr};
   bool sweep_recorded = false;
-  // side stream (default priority) for work that may run beside the caller's stream:
-  // side_ev[0] forks it, side_ev[1] marks its end
-  hipStream_t side = nullptr;
-  hipEvent_t side_ev[2] = {nullptr, nullptr};
-  bool side_pending = false;
   int rank1_form = TTNN_R1_TERMWISE;       // how rank-1 updates form X_t^T v_t
   // transposed DRM copies (Xt, Yt, Xt64) for the MFMA forms of whole-tensor updates:
   // reserved at creation, filled from the FP64 masters by the first whole-tensor update
