@@ -70,3 +70,36 @@ def test_large_strided_box_packed(P, variant, dtype):
     assert _same(_sketches(P, d), _sketches(P, e))
     for p in (a, b, c, d, e):
         p.close()
+
+
+@pytest.mark.parametrize("dims,ext,off", [((257, 129, 130), (255, 129, 129), (1, 0, 1)),
+                                          ((4200000, 1, 3), (4194305, 1, 2), (5, 0, 1)),
+                                          ((3, 1500000, 2), (1, 1500000, 2), (2, 0, 0)),
+                                          ((3, 2097153, 2), (2, 2097153, 1), (1, 0, 1))])
+def test_packed_strided_edges(P, dims, ext, off):
+    """Long and short first modes, modes of extent 1, and boxes that end inside a unit of the
+    packing kernel: bitwise the sketch of the packed copy."""
+    tree = ((1, 2), 3)
+    X = torch.randn(dims[::-1], dtype=torch.float64, device="cuda")
+    view = X[tuple(slice(o, o + e) for o, e in zip(off[::-1], ext[::-1]))]
+    a, b = (P.Plan(tree, dims, 2, 1, variant="ttnn", dtype="f64", seed=5) for _ in range(2))
+    a.update(view, extent=ext, offset=off)
+    b.update(view.contiguous(), extent=ext, offset=off)
+    torch.cuda.synchronize()
+    for modes in ((1,), (2,), (3,), (1, 2)):
+        x, y = (p.read_sketch(p.node(modes), P.SK_R).cpu().numpy() for p in (a, b))
+        assert np.array_equal(x.view(np.uint64), y.view(np.uint64)), modes
+
+
+def test_packed_in_halves(P):
+    """A box of more than 2^30 entries is packed in parts: bitwise the packed copy's sketch."""
+    tree, dims, ext, off = ((1, 2), 3), (1030, 1024, 1030), (1025, 1024, 1025), (2, 0, 3)
+    X = torch.randn(dims[::-1], dtype=torch.bfloat16, device="cuda")
+    view = X[tuple(slice(o, o + e) for o, e in zip(off[::-1], ext[::-1]))]
+    a, b = (P.Plan(tree, dims, 2, 1, variant="ttnn", dtype="bf16", seed=5) for _ in range(2))
+    a.update(view, extent=ext, offset=off)
+    b.update(view.contiguous(), extent=ext, offset=off)
+    torch.cuda.synchronize()
+    for modes in ((1,), (2,), (3,), (1, 2)):
+        x, y = (p.read_sketch(p.node(modes), P.SK_R).cpu().numpy() for p in (a, b))
+        assert np.isfinite(x).all() and np.array_equal(x.view(np.uint64), y.view(np.uint64)), modes
