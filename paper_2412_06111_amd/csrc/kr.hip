@@ -10,163 +10,171 @@
 // vectors of a child.  Split the reduction index into the first non-output axis a
 // (size n0) and the rest e (the outer combinations):
 //   out[o, j] = sum_e w_e[j] sum_a C_e[o, a] F_0[a, j],  w_e[j] = prod_{q>=1} F_q[e_q, j],
-// a GEMM per outer combination, scaled by column and accumulated.  A workgroup owns a
-// 32 (o) x 64 (j) tile; per unit (one outer combination, one chunk of at most 32 values
-// of a, the chunks of equal length) it stages C_e (chunk x 32) and F_0 (chunk x 64) in
-// LDS, loading the next unit into registers while it computes, and every thread
-// accumulates a 2 x 4 register block in FP64 (VALU).  The units are cut into G contiguous slices, one workgroup
-// each; for G > 1 a second kernel adds the G partials in a fixed order, so the result
-// depends only on the shapes.
+// one contraction over (a, e) whose right operand F_0[a, j] w_e[j] is formed in registers.
+// It runs on the FP64 MFMA, operands straight from global memory (a core is read once, the
+// factors stay in the caches): a wave takes 32 values of o (two row blocks) by up to 64
+// columns and a contiguous slice of the steps, four values of a of one combination each,
+// loading four steps ahead.  The four waves of a workgroup take neighbouring slices and add
+// their sums in wave order through LDS; the steps are cut into 4 G slices, and for G > 1 a
+// second kernel adds the G partials in a fixed order, so the result depends only on the
+// shapes.
+//
+// Bound by latency: the six 70^3 cores of a 500^6 tensor's tree are 1 to 4 us of MFMA work a
+// level.  A level took 24-30 us on FP64 VALU products of LDS tiles (seven serial units of a
+// load, a barrier and 24 steps); now 10-17.
 #include "kr.hpp"
+
+#include <algorithm>
+
+#include "mfma.hpp"
 
 namespace ttnn {
 
 namespace {
 
-constexpr int kTO = 32, kTJ = 64, kKC = 32;   // kKC: longest chunk of the inner axis per unit
-constexpr int kCLD = kTO + 2;                  // LDS row of C: padded, 16-byte aligned
-constexpr int kCR = kKC * kTO / 256, kFR = kKC * kTJ / 256;
+constexpr int kTO = 32, kTJ = 64;          // values of o and columns (at most) of a workgroup
+constexpr int kAhead = 4;                  // steps of loads in flight
 
-// Chunks of the inner axis: as few as hold n0 in chunks of at most kKC, of equal length.
-__host__ __device__ inline int64_t kr_nchunks(int64_t n0) { return (n0 + kKC - 1) / kKC; }
-__host__ __device__ inline int kr_chunk(int64_t n0) {
-  const int64_t nch = kr_nchunks(n0);
-  return static_cast<int>((n0 + nch - 1) / nch);
-}
-
-__global__ __launch_bounds__(256) void kr_contract_kernel(KJobList L) {
+template <int NCB>
+__global__ __launch_bounds__(256) void kr_contract_kernel(KJobList) {
+  using P = Pol<TTNN_F64>;
+  // the job's fields by scalar loads (indexing a by-value argument would copy it to scratch)
+  typedef const KJobList __attribute__((address_space(4))) ConstList;
+  ConstList& L = *(ConstList*)__builtin_amdgcn_kernarg_segment_ptr();
   const int64_t b = blockIdx.x;
   int jid = 0;
   while (jid + 1 < L.n && b >= L.jobs[jid + 1].first_block) ++jid;
-  const KJob& J = L.jobs[jid];
+  const auto& J = L.jobs[jid];
   int64_t local = b - J.first_block;
-  const int64_t jt = local % J.colchunks;
+  const int j0 = static_cast<int>(local % J.colchunks) * 16 * NCB;
   local /= J.colchunks;
-  const int64_t ot = local % J.otiles;
+  const int64_t o0 = (local % J.otiles) * kTO;
   const int64_t g = local / J.otiles;
-  const int64_t so = J.size[J.oax];
-  const int cols = J.cols;
-  const int tid = threadIdx.x;
-  const int tj = tid & 15, to = tid >> 4;
-  const int64_t o0 = ot * kTO, j0 = jt * kTJ;
+  const int oax = J.oax, naxes = J.naxes, cols = J.cols;
+  const int64_t so = J.size[oax];
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  int ax[kMaxAxes];
-  int na = 0;
-  int64_t stride[kMaxAxes];
-  int64_t sz = 1;
-  for (int q = 0; q < J.naxes; ++q) {
-    stride[q] = sz;
-    sz *= J.size[q];
-    if (q != J.oax) ax[na++] = q;
+  const int in = oax == 0 ? 1 : 0;          // the inner axis; none when there is only the output axis
+  const bool one = in >= naxes;
+  const int64_t n0 = one ? 1 : J.size[in];
+  const double* F0 = one ? nullptr : J.fac[in];
+  int64_t so_stride = 1;
+  for (int q = 0; q < oax; ++q) so_stride *= J.size[q];
+  const int64_t st0 = in == 0 ? 1 : so;
+  const int64_t nst = (n0 + 3) / 4, steps = J.kred / n0 * nst;
+  const int64_t slice = 4 * g + wave;
+  const int64_t hi = steps * (slice + 1) / (4 * J.G);
+  int64_t at = steps * slice / (4 * J.G);    // the next step to load: values 4 t.. of combination e
+  int64_t e = at / nst, t = at - e * nst;
+
+  // Rows past the end read the last row and columns past the end the last column: what they
+  // form is not delivered.
+  const double* row[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int64_t o = o0 + 16 * i + l16;
+    row[i] = J.core + (o < so ? o : so - 1) * so_stride;
   }
-  const int64_t n0 = na ? J.size[ax[0]] : 1;
-  const int64_t st0 = na ? stride[ax[0]] : 0;
-  const double* F0 = na ? J.fac[ax[0]] : nullptr;
-  const int64_t nch = kr_nchunks(n0);
-  const int kc = kr_chunk(n0);
-  const int64_t units = (J.kred / n0) * nch;
-  const int64_t ulo = units * g / J.G, uhi = units * (g + 1) / J.G;
-  const int64_t so_stride = stride[J.oax];
-
-  __shared__ __attribute__((aligned(16))) double Cs[kKC * kCLD];
-  __shared__ __attribute__((aligned(16))) double Fs[kKC * kTJ];
-
-  // the unit being loaded: outer combination (digits, core offset, column weights) and chunk
-  int64_t dig[kMaxAxes] = {};
-  int64_t eL = -1, offL = 0;
-  double wL[4] = {1.0, 1.0, 1.0, 1.0};
-  double cr[kCR], fr[kFR];
-  auto load = [&](int64_t u) {
-    const int64_t e = u / nch, c0 = u % nch;
-    if (e != eL) {
-      if (eL < 0) {
-        int64_t rest = e;
-        for (int q = 1; q < na; ++q) {
-          dig[q] = rest % J.size[ax[q]];
-          rest /= J.size[ax[q]];
-        }
-      } else {
-        for (int q = 1; q < na; ++q) {
-          if (++dig[q] < J.size[ax[q]]) break;
-          dig[q] = 0;
-        }
-      }
-      eL = e;
-      offL = 0;
-      for (int q = 1; q < na; ++q) offL += dig[q] * stride[ax[q]];
-      for (int i = 0; i < 4; ++i) {
-        const int64_t j = j0 + 4 * tj + i;
-        double v = 1.0;
-        if (j < cols)
-          for (int q = 1; q < na; ++q) v *= J.fac[ax[q]][dig[q] * cols + j];
-        wL[i] = v;
-      }
-    }
-    const int64_t a0 = c0 * kc;
-    const int64_t alim = (n0 - a0) < kc ? (n0 - a0) : kc;
+  int jc[NCB];
 #pragma unroll
-    for (int i = 0; i < kCR; ++i) {            // C_e[o0 .. o0 + 32, a0 .. a0 + kc): a fastest
-      const int idx = tid + 256 * i;
-      const int a = idx % kKC, o = idx / kKC;
-      double v = 0.0;
-      if (o0 + o < so && a < alim) v = J.core[(o0 + o) * so_stride + offL + (a0 + a) * st0];
-      cr[i] = v;
+  for (int cb = 0; cb < NCB; ++cb) jc[cb] = j0 + 16 * cb + l16 < cols ? j0 + 16 * cb + l16 : cols - 1;
+
+  // Up to kAhead steps of one combination: operands and, per column, the other axes' product
+  struct Block {
+    double a[2][kAhead], f[NCB][kAhead], w[NCB];
+    int n;                                   // steps in it
+    int64_t last;                            // values of a from its first on
+  };
+  auto fetch = [&](Block& k) {
+    k.n = 0;
+    if (at >= hi) return;
+    int64_t n = nst - t < hi - at ? nst - t : hi - at;
+    k.n = static_cast<int>(n < kAhead ? n : kAhead);
+    k.last = n0 - 4 * t;
+    int64_t off = 0, rest = e, stride = 1;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) k.w[cb] = 1.0;
+    for (int q = 0; q < naxes; ++q) {
+      const int64_t sz = J.size[q];
+      if (q != oax && q != in) {
+        const int64_t up = rest / sz, d = rest - up * sz;
+        rest = up;
+        off += d * stride;
+        const double* F = J.fac[q] + d * cols;
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) k.w[cb] *= F[jc[cb]];
+      }
+      stride *= sz;
     }
 #pragma unroll
-    for (int i = 0; i < kFR; ++i) {            // F_0[a0 .. a0 + kc, j0 .. j0 + 64): j fastest
-      const int idx = tid + 256 * i;
-      const int j = idx % kTJ, a = idx / kTJ;
-      double v = 0.0;
-      if (j0 + j < cols && a < alim) v = F0 ? F0[(a0 + a) * cols + j0 + j] : 1.0;
-      fr[i] = v;
+    for (int u = 0; u < kAhead; ++u) {
+      // past the block or past n0: the first value, zeroed before its product
+      const int64_t v = 4 * (t + u) + lg, a = u < k.n && v < n0 ? v : 0;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) k.a[i][u] = row[i][off + a * st0];
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) k.f[cb][u] = F0 ? F0[a * cols + jc[cb]] : 1.0;
+    }
+    at += k.n;
+    t += k.n;
+    if (t == nst) {
+      t = 0;
+      ++e;
     }
   };
-
-  double acc[2][4] = {};
-  if (ulo < uhi) load(ulo);
-  for (int64_t u = ulo; u < uhi; ++u) {
-    const double w[4] = {wL[0], wL[1], wL[2], wL[3]};
-    const int64_t c0 = u % nch;
-    const int arun = static_cast<int>((n0 - c0 * kc) < kc ? (n0 - c0 * kc) : kc);
+  f64x4_t acc[2][NCB];
 #pragma unroll
-    for (int i = 0; i < kCR; ++i) {
-      const int idx = tid + 256 * i;
-      Cs[(idx % kKC) * kCLD + idx / kKC] = cr[i];
-    }
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int i = 0; i < kFR; ++i) {
-      const int idx = tid + 256 * i;
-      Fs[(idx / kTJ) * kTJ + idx % kTJ] = fr[i];
+    for (int cb = 0; cb < NCB; ++cb) acc[i][cb] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  auto products = [&](const Block& k) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (u >= k.n) break;
+      const bool live = 4 * u + lg < k.last;
+      double x[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) x[i] = live ? k.a[i][u] : 0.0;
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) {
+        if (j0 + 16 * cb >= cols) continue;
+        const double y = live ? k.f[cb][u] * k.w[cb] : 0.0;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[i][cb] = P::mfma(x[i], y, acc[i][cb]);
+      }
     }
-    __syncthreads();
-    if (u + 1 < uhi) load(u + 1);              // next unit's loads overlap this unit's arithmetic
-    double t[2][4] = {};
-    for (int a = 0; a < arun; ++a) {
-      const double2 c = *reinterpret_cast<const double2*>(&Cs[a * kCLD + 2 * to]);
-      const double2 f01 = *reinterpret_cast<const double2*>(&Fs[a * kTJ + 4 * tj]);
-      const double2 f23 = *reinterpret_cast<const double2*>(&Fs[a * kTJ + 4 * tj + 2]);
-      t[0][0] = fma(c.x, f01.x, t[0][0]);
-      t[0][1] = fma(c.x, f01.y, t[0][1]);
-      t[0][2] = fma(c.x, f23.x, t[0][2]);
-      t[0][3] = fma(c.x, f23.y, t[0][3]);
-      t[1][0] = fma(c.y, f01.x, t[1][0]);
-      t[1][1] = fma(c.y, f01.y, t[1][1]);
-      t[1][2] = fma(c.y, f23.x, t[1][2]);
-      t[1][3] = fma(c.y, f23.y, t[1][3]);
-    }
-    for (int i = 0; i < 2; ++i)
-      for (int jj = 0; jj < 4; ++jj) acc[i][jj] = fma(w[jj], t[i][jj], acc[i][jj]);
-    __syncthreads();
+  };
+  Block k0, k1;
+  fetch(k0);
+  while (k0.n) {
+    fetch(k1);
+    products(k0);
+    if (!k1.n) break;
+    fetch(k0);
+    products(k1);
   }
-  for (int i = 0; i < 2; ++i) {
-    const int64_t o = o0 + 2 * to + i;
-    if (o >= so) continue;
-    for (int jj = 0; jj < 4; ++jj) {
-      const int64_t j = j0 + 4 * tj + jj;
-      if (j >= cols) continue;
-      if (J.G == 1) J.out[o * cols + j] = acc[i][jj];
-      else J.part[(g * so + o) * cols + j] = acc[i][jj];
+
+  // the four waves' sums, added in wave order
+  __shared__ double red[4][8][64];
+  for (int cb = 0; cb < NCB; ++cb) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[wave][4 * i + v][lane] = acc[i][cb][v];
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int x = wave + 4 * h;            // row block x / 4, result x % 4 of this lane
+      const double sum = red[0][x][lane] + red[1][x][lane] + red[2][x][lane] + red[3][x][lane];
+      const int64_t o = o0 + 16 * (x / 4) + P::crow(lane, x % 4);
+      const int64_t j = j0 + 16 * cb + l16;
+      if (o < so && j < cols) {
+        if (J.G == 1) J.out[o * cols + j] = sum;
+        else J.part[(g * so + o) * cols + j] = sum;
+      }
     }
+    __syncthreads();
   }
 }
 
@@ -199,9 +207,9 @@ __global__ __launch_bounds__(256) void kr_fold_kernel(KJobList L) {
 
 int kr_split(int64_t so, int cols, int64_t n0, int64_t nouter) {
   const int64_t tiles = ((so + kTO - 1) / kTO) * ((cols + kTJ - 1) / kTJ);
-  const int64_t units = nouter * kr_nchunks(n0);
+  const int64_t steps = nouter * ((n0 + 3) / 4);
   int64_t G = tiles >= 512 ? 1 : 512 / tiles;
-  if (G > units / 2) G = units / 2;                    // at least two units per slice
+  if (G > steps / 32) G = steps / 32;                  // at least eight steps a wave
   if (G > 32) G = 32;                                  // the fold reads G partials per output
   return G < 1 ? 1 : static_cast<int>(G);
 }
@@ -214,12 +222,15 @@ void launch_kr_contract(std::vector<KJob> jobs, hipStream_t stream) {
   for (size_t at = 0; at < jobs.size(); at += kMaxKJobs) {
     KJobList L{};
     int64_t blocks = 0, fblocks = 0;
+    int width = 1;                                     // 16-column blocks of a workgroup
+    for (size_t i = at; i < jobs.size() && i < at + kMaxKJobs; ++i)
+      width = std::max(width, std::min((jobs[i].cols + 15) / 16, kTJ / 16));
     for (size_t i = at; i < jobs.size() && L.n < kMaxKJobs; ++i) {
       KJob j = jobs[i];
       TTNN_REQUIRE(j.naxes >= 1 && j.naxes <= kMaxAxes && j.oax >= 0 && j.oax < j.naxes && j.cols >= 1,
                    TTNN_E_INVALID, "bad tree contraction");
       TTNN_REQUIRE(j.G == 1 || j.part != nullptr, TTNN_E_INVALID, "split tree contraction without scratch");
-      j.colchunks = (j.cols + kTJ - 1) / kTJ;
+      j.colchunks = (j.cols + 16 * width - 1) / (16 * width);
       j.otiles = (j.size[j.oax] + kTO - 1) / kTO;
       j.kred = 1;
       for (int q = 0; q < j.naxes; ++q)
@@ -232,7 +243,13 @@ void launch_kr_contract(std::vector<KJob> jobs, hipStream_t stream) {
       }
       L.jobs[L.n++] = j;
     }
-    if (blocks > 0) kr_contract_kernel<<<dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream>>>(L);
+    const dim3 grid(static_cast<unsigned>(blocks));
+    if (blocks > 0) {
+      if (width == 1) kr_contract_kernel<1><<<grid, dim3(256), 0, stream>>>(L);
+      else if (width == 2) kr_contract_kernel<2><<<grid, dim3(256), 0, stream>>>(L);
+      else if (width == 3) kr_contract_kernel<3><<<grid, dim3(256), 0, stream>>>(L);
+      else kr_contract_kernel<4><<<grid, dim3(256), 0, stream>>>(L);
+    }
     if (fblocks > 0) kr_fold_kernel<<<dim3(static_cast<unsigned>(fblocks)), dim3(256), 0, stream>>>(L);
   }
 }

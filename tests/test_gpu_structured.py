@@ -190,3 +190,20 @@ def test_rounding_workload_parity(P, rounding, r):
         e = errs2(hc[m], ocm[m])
         assert e[0] <= 1e-8, (m, e)
     plan.close()
+
+
+@pytest.mark.parametrize("s", [1, 5, 33, 70])
+@pytest.mark.parametrize("r,p", [(16, 1), (31, 2), (64, 65)])
+def test_contraction_tile_edges(P, s, r, p):
+    """Ranks and widths at the edges of the contraction kernel's row blocks, column blocks,
+    steps of four and slices; a mode of size 1 and one with no whole step."""
+    spec, dims = O.TOY, (130, 1, 3, 37, 64, 9)
+    cores = W.gaussian_ttn_cores(spec, dims, s, seed=2)
+    tree = O.Tree(spec, dims, r, p)
+    X, Y = S.factors(4, dims, r, p)
+    plan = P.Plan(spec, dims, r, p, variant="kr", seed=4)
+    plan.update_ttn(dev_cores(cores), s)
+    torch.cuda.synchronize()
+    bad = failures(sketch_errors(plan, tree, S.ttn_sketch(cores, tree, X, Y)), TOL["f64"])
+    assert not bad, bad
+    plan.close()
