@@ -1348,6 +1348,233 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_f64_kernel(SttnnArgs a) {
       }
 }
 
+// ---------------------------------------------------------------- BF16 Z1-out at r = 64, four slabs
+// Bound by its bytes: for a 128^4 tensor 0.8 GB read (T, X_1) and 1.0 GB written (Z1 in FP32,
+// the partials of Z_A, which halve with four slabs a tile in place of two).  The roles are
+// those of sttnn_t4_f64_kernel: waves 0, 1 Z_A and the copies of T and X_1, three sub-tiles
+// ahead into four stages, and of X_A, a column block ahead; waves 2, 3 Z1, Y_1 in registers,
+// written straight from the products; waves 4-7 R_A and R_1.  The Y_A rows of the four slabs
+// (96 KB) stay in LDS.
+// 128^4, r = 64: the sweep 540 -> 440 us and the reduction of its partials 103 -> 63, the
+// whole update 1083 -> 944 (sttnn_t4_kernel: two slabs, Z1 through an LDS stash, every wave
+// waiting for its copies; with the X values fetched by waves 4-7 a sub-tile ahead: 583).
+struct Bf64Layout {
+  static constexpr int R = 64, KP = 96, B2 = 4, SC = 32, NST = 4;
+  static constexpr size_t MT = size_t(SC) * N1 * 2, MX = size_t(R) * SC * 2;
+  static constexpr size_t MS = MT + MX;                       // one stage: T, then X_1
+  static constexpr size_t OFF_XA = NST * MS;                  // X_A of two column blocks
+  static constexpr size_t OFF_YR = OFF_XA + 2 * MX;
+  static constexpr size_t TOTAL = OFF_YR + size_t(B2) * KP * N1 * 2;
+  static_assert(TOTAL <= 160 * 1024, "LDS");
+};
+
+__global__ __launch_bounds__(kThreadsF) void sttnn_t4_bf64_kernel(SttnnArgs a) {
+  using Lay = Bf64Layout;
+  using P = Pol<TTNN_BF16>;
+  constexpr int R = Lay::R, KP = Lay::KP, B2 = Lay::B2, SC = Lay::SC, NST = Lay::NST;
+  constexpr int CBR = R / 16, KB = KP / 16, NCB = SC / 16, NK = N1 / 32;
+  using Z = Swz<uint16_t, N1>;
+  using ZX = Swz<uint16_t, SC>;
+  __shared__ __align__(16) char smem[Lay::TOTAL];
+  uint16_t* YRs = reinterpret_cast<uint16_t*>(smem + Lay::OFF_YR);
+
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tA, tB;
+  tile_of(a, tA, tB);
+  const int64_t i2_0 = static_cast<int64_t>(tA) * B2;
+  const int64_t c_tile = static_cast<int64_t>(tB) * a.CB * SC;
+  const int64_t nA = a.nA, nB = a.nB, n2 = a.n2;
+  const int nsub = a.CB * B2;
+  static_assert(B2 == 4 && NCB == 2 && NST == 4 && Z::CPR == 16 && KB == 6, "the loops' slabs, roles and counts");
+  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+
+  auto stage = [&](int s) { return reinterpret_cast<uint16_t*>(smem + (s % NST) * Lay::MS); };
+  auto stage_x1 = [&](int s) { return stage(s) + SC * N1; };
+  auto stage_xa = [&](int cb) { return reinterpret_cast<uint16_t*>(smem + Lay::OFF_XA + (cb % 2) * Lay::MX); };
+  auto frag = [&](const uint16_t* rows, int r, int k) { return P::load8(&rows[Z::off(r, k)]); };
+#pragma unroll
+  for (int i = 0; i < B2; ++i)
+    lds_dma_rows<uint16_t, N1>(static_cast<const uint16_t*>(a.YA) + (i2_0 + i) * N1, nA, YRs + i * KP * N1, KP, wave,
+                               lane);
+  __syncthreads();                          // the resident rows are there
+  auto next_stage = [&]() {
+    lds_wait_all();                         // this wave's reads of the last stage are done
+    raw_barrier();
+  };
+
+  if (wave < 4) {
+    const int iBl = 16 * (wave % NCB) + l16;
+    if (wave < NCB) {
+      const uint16_t* T = static_cast<const uint16_t*>(a.T);
+      const uint16_t* XA = static_cast<const uint16_t*>(a.XA);
+      const uint16_t* X1 = static_cast<const uint16_t*>(a.X1);
+      // A wave's loads of sub-tile s, four of T and two of X_1 (past the last sub-tile, of the
+      // last one into a stage that nobody reads, so that the loads in flight are the same in
+      // every sub-tile), and its two of a column block's X_A.
+      auto issue = [&](int s) {
+        constexpr int RPI = 64 / Z::CPR, RPX = 64 / ZX::CPR;
+        const int e = s < nsub ? s : nsub - 1;
+        const int64_t i2 = i2_0 + e % B2, col = c_tile + static_cast<int64_t>(e / B2) * SC;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int q = 2 * u + wave, r = q * RPI + lane / Z::CPR;
+          lds_dma16(T + i2 * N1 + nA * (col + r) + ((lane % Z::CPR) ^ (r & Z::MASK)) * Z::EV, stage(s) + q * RPI * N1);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int q = 2 * u + wave, r = q * RPX + lane / ZX::CPR;
+          lds_dma16(X1 + (r * n2 + i2) * nB + col + ((lane % ZX::CPR) ^ (r & ZX::MASK)) * ZX::EV,
+                    stage_x1(s) + q * RPX * SC);
+        }
+      };
+      auto issue_xa = [&](int cb) {
+        constexpr int RPX = 64 / ZX::CPR;
+        const int64_t col = c_tile + static_cast<int64_t>(cb < a.CB ? cb : a.CB - 1) * SC;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int q = 2 * u + wave, r = q * RPX + lane / ZX::CPR;
+          lds_dma16(XA + r * nB + col + ((lane % ZX::CPR) ^ (r & ZX::MASK)) * ZX::EV, stage_xa(cb) + q * RPX * SC);
+        }
+      };
+      f32x4_t zA[KB];
+      float* PZ = static_cast<float*>(a.PZA) + static_cast<int64_t>(tA) * KP * nB + c_tile + iBl;
+      issue_xa(0);
+#pragma unroll
+      for (int s = 0; s < NST - 1; ++s) issue(s);
+      for (int cb = 0; cb < a.CB; ++cb) {
+#pragma unroll
+        for (int rb = 0; rb < KB; ++rb) zA[rb] = zero;
+#pragma unroll
+        for (int i2l = 0; i2l < B2; ++i2l) {
+          // The copies of this sub-tile have to have landed.  Loads and stores complete in
+          // order, and after those copies, issued three sub-tiles ago, come the twelve of the
+          // next two, the two of X_A if a column block began in between, and the 24 stores of
+          // a column block that ended since.
+          if (i2l == 0) {
+            if (cb > 0) __builtin_amdgcn_s_waitcnt(0x8074);             // vmcnt(36) lgkmcnt(0)
+            else __builtin_amdgcn_s_waitcnt(0x007c);                    // vmcnt(12) lgkmcnt(0)
+          } else if (i2l < 3) {
+            if (cb > 0) __builtin_amdgcn_s_waitcnt(0x8076);             // vmcnt(38) lgkmcnt(0)
+            else __builtin_amdgcn_s_waitcnt(0x007e);                    // vmcnt(14) lgkmcnt(0)
+          } else {
+            __builtin_amdgcn_s_waitcnt(0x007c);                         // vmcnt(12) lgkmcnt(0)
+          }
+          raw_barrier();                    // everyone's reads of the stages filled now are done
+          if (i2l == 0) issue_xa(cb + 1);
+          issue(cb * B2 + i2l + NST - 1);
+          __builtin_amdgcn_sched_barrier(0);
+          const uint16_t* Ms = stage(cb * B2 + i2l);
+          const uint16_t* Ys = YRs + i2l * KP * N1;
+          bf16x8_t b[2], y[2][KB];
+          auto load = [&](int t, int q) {
+            b[q] = frag(Ms, iBl, 32 * t + 8 * lg);
+#pragma unroll
+            for (int rb = 0; rb < KB; ++rb) y[q][rb] = frag(Ys, 16 * rb + l16, 32 * t + 8 * lg);
+          };
+          load(0, 0);
+#pragma unroll
+          for (int t = 0; t < NK; ++t) {
+            lds_wait_all();
+            if (t + 1 < NK) load(t + 1, (t + 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int rb = 0; rb < KB; ++rb) zA[rb] = P::mfma(y[t & 1][rb], b[t & 1], zA[rb]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+#pragma unroll
+        for (int rb = 0; rb < KB; ++rb)     // the tile's row range of Z_A for these columns
+#pragma unroll
+          for (int v = 0; v < 4; ++v) PZ[(16 * rb + P::crow(lane, v)) * nB + cb * SC] = zA[rb][v];
+      }
+      __builtin_amdgcn_s_waitcnt(0);        // no copy outlives the workgroup
+      return;
+    }
+    bf16x8_t y[NK][KB];
+    const uint16_t* Y1 = static_cast<const uint16_t*>(a.Y1) + l16 * N1 + 8 * lg;
+#pragma unroll
+    for (int t = 0; t < NK; ++t)
+#pragma unroll
+      for (int rb = 0; rb < KB; ++rb) y[t][rb] = P::load8(Y1 + 16 * rb * N1 + 32 * t);
+    float* PZ = static_cast<float*>(a.Z1) + (i2_0 * nB + c_tile + iBl) * KP + 4 * lg;
+    for (int s = 0; s < nsub; ++s) {
+      f32x4_t z1[KB];
+#pragma unroll
+      for (int rb = 0; rb < KB; ++rb) z1[rb] = zero;
+      next_stage();
+      const uint16_t* Ms = stage(s);
+      bf16x8_t b[NK];
+#pragma unroll
+      for (int t = 0; t < NK; ++t) b[t] = frag(Ms, iBl, 32 * t + 8 * lg);
+#pragma unroll
+      for (int t = 0; t < NK; ++t)
+#pragma unroll
+        for (int rb = 0; rb < KB; ++rb) z1[rb] = P::mfma(y[t][rb], b[t], z1[rb]);
+      float* o = PZ + ((s % B2) * nB + (s / B2) * SC) * KP;
+#pragma unroll
+      for (int rb = 0; rb < KB; ++rb) *reinterpret_cast<f32x4_t*>(o + 16 * rb) = z1[rb];
+    }
+    return;
+  }
+
+  // R_A and R_1: A = slab (rows i1, K = the sub-tile's 32 columns, 8 lg + e of the lane)
+  f32x4_t rA[2][B2][CBR], r1[2][CBR];       // [i1 block][slab][column block]
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < CBR; ++c) {
+      r1[h][c] = zero;
+#pragma unroll
+      for (int i = 0; i < B2; ++i) rA[h][i][c] = zero;
+    }
+  const int i1base = 32 * (wave - 4);
+  bf16x8_t xa[CBR];
+  for (int cb = 0; cb < a.CB; ++cb) {
+#pragma unroll
+    for (int i2l = 0; i2l < B2; ++i2l) {
+      next_stage();
+      const uint16_t* Ms = stage(cb * B2 + i2l);
+      bf16x8_t v[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        u16x8_t w;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = Ms[Z::off(8 * lg + e, i1base + 16 * h + l16)];
+        v[h] = __builtin_bit_cast(bf16x8_t, w);
+      }
+      bf16x8_t x1[CBR];
+#pragma unroll
+      for (int c = 0; c < CBR; ++c) {
+        const int o = ZX::off(16 * c + l16, 8 * lg);
+        x1[c] = P::load8(stage_x1(cb * B2 + i2l) + o);
+        if (i2l == 0) xa[c] = P::load8(stage_xa(cb) + o);
+      }
+#pragma unroll
+      for (int c = 0; c < CBR; ++c)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          r1[h][c] = P::mfma(v[h], x1[c], r1[h][c]);
+          rA[h][i2l][c] = P::mfma(v[h], xa[c], rA[h][i2l][c]);
+        }
+    }
+  }
+  float* PRA = static_cast<float*>(a.PRA);
+  float* PR1 = static_cast<float*>(a.PR1);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < CBR; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i1 = i1base + 16 * h + P::crow(lane, v), j = 16 * c + l16;
+#pragma unroll
+        for (int i = 0; i < B2; ++i)
+          PRA[(static_cast<int64_t>(tB) * nA + (i2_0 + i) * N1 + i1) * R + j] = rA[h][i][c][v];
+        PR1[((static_cast<int64_t>(tA) * a.TB + tB) * N1 + i1) * R + j] = r1[h][c][v];
+      }
+}
+
 // sum_{t < n} p[t * stride] in FP64 with eight interleaved partial sums (t mod 8),
 // combined in a fixed order: eight loads in flight per thread.
 template <typename Acc>
@@ -1555,6 +1782,10 @@ void launch_sttnn(bool tt, bool zout, const SttnnArgs& a, hipStream_t st) {
   if (tt) hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2T, SC, true, false>), grid, dim3(kThreadsF), 0, st, a);
   else if (zout && DT == TTNN_F64 && R == 32) hipLaunchKernelGGL(sttnn_t4_f64_kernel, grid, dim3(kThreadsF), 0, st, a);
   else if (zout) {
+    if (DT == TTNN_BF16 && R == 64 && a.n2 == int64_t(a.TA) * Bf64Layout::B2) {
+      hipLaunchKernelGGL(sttnn_t4_bf64_kernel, grid, dim3(kThreadsF), 0, st, a);
+      return;
+    }
     if constexpr (DT != TTNN_F64 || R != 32)
       hipLaunchKernelGGL((sttnn_t4_kernel<DT, R, KP, B2Z, SCZ, false, true>), grid, dim3(kThreadsF), 0, st, a);
   }
@@ -1601,7 +1832,9 @@ void fused_prepare(Plan& P, hipStream_t st) {
   // (a BF16 plan writes Z1 in FP32 and contracts it with an FP32 copy of X_2)
   const int zdt = P.dtype == TTNN_BF16 ? TTNN_F32 : P.dtype;
   const bool zout = !tt && R >= 32 && right_mfma_eligible(static_cast<int64_t>(KP) * nB, n2, 1, R, zdt);
-  const Shape sh = shape_for(P.dtype, R, tt, zout);
+  Shape sh = shape_for(P.dtype, R, tt, zout);
+  // sttnn_t4_bf64_kernel where four slabs a tile divide n_2 (the two-slab form where two do)
+  if (P.dtype == TTNN_BF16 && R == 64 && zout && n2 % Bf64Layout::B2 == 0) sh.B2 = Bf64Layout::B2;
   if (n2 % sh.B2 != 0 || nB % sh.SC != 0) return;
   const int TA = static_cast<int>(n2 / sh.B2);
   // column tiles: the fewest that give every compute unit a tile (else as many as divide)

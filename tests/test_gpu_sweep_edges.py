@@ -26,3 +26,19 @@ def test_role_split_sweep_edges(dims, p, variant, dtype):
     sk = O.sketch(consumed, tree, O.DRMs(tree, 9, variant, dtype), variant)
     bad = failures(sketch_errors(plan, tree, sk), TOL_ARITH[dtype])
     assert not bad, bad
+
+
+@pytest.mark.parametrize("dims", [(128, 4, 16, 64), (128, 12, 24, 24), (128, 6, 8, 32), (128, 68, 16, 64)], ids=str)
+@pytest.mark.parametrize("p", [1, 32])
+def test_bf16_sweep_edges(dims, p):
+    """BF16 at r = 64: four slabs a tile where n_2 allows, else two."""
+    import paper_2412_06111_amd as P
+    T = np.random.default_rng(22).standard_normal(dims)
+    dev, consumed = to_device(T, "bf16")
+    plan = P.Plan(O.T4, dims, 64, p, variant="sttnn", dtype="bf16", seed=9)
+    plan.update(dev, alpha=0.5)
+    plan.update(dev, alpha=0.5)
+    tree = O.Tree(O.T4, dims, 64, p)
+    sk = O.sketch(consumed, tree, O.DRMs(tree, 9, "sttnn", "bf16"), "sttnn")
+    bad = failures(sketch_errors(plan, tree, sk), TOL_ARITH["bf16"])
+    assert not bad, bad
