@@ -17,8 +17,8 @@
 
 namespace ttnn {
 
-// d_flag: [0] non-finite count, [1, nn) kept singular values per node, then the call
-// and sticky status words at the end of the array
+// d_flag: [0, nn) kept singular values per node, then the call and sticky status words at
+// the end of the array
 constexpr int kCallWord = 2 * TTNN_MAX_NODES - 2, kStickyWord = 2 * TTNN_MAX_NODES - 1;
 
 namespace {
@@ -874,9 +874,8 @@ void enqueue_assemble(Plan& P, double* const* cores, hipStream_t st) {
   if (!P.epilogue_valid) run_epilogue(P, st);
   const int nn = static_cast<int>(P.nodes.size());
   // finite check of the sketches
-  launch_zero_int(P.d_flag, kCallWord, st);
+  SegList s;
   {
-    SegList s;
     for (int v = 1; v < nn; ++v) {
       const Node& t = P.nodes[v];
       if (t.ident) continue;
@@ -887,7 +886,7 @@ void enqueue_assemble(Plan& P, double* const* cores, hipStream_t st) {
       }
     }
     s.push(P.psi_root, P.psi_root_len);
-    launch_finite_list(s, P.d_flag, st);
+    launch_finite_list(s, P.d_finite, st);
   }
 
   QrJobList jl{};
@@ -897,7 +896,7 @@ void enqueue_assemble(Plan& P, double* const* cores, hipStream_t st) {
     jl.jobs[jl.n] = QrJob{t.Om, t.Q, t.Pinv, t.k, t.r, jl.n};
     ++jl.n;
   }
-  launch_qr_pinv(jl, P.eps_factor, P.d_flag + 1, st);
+  launch_qr_pinv(jl, P.eps_factor, P.d_flag, st);
 
   // cores: leaves B = Psi Pinv; internal nodes and root contract Psi with Q_c^T child by
   // child, then (non-root) apply Pinv.
@@ -950,7 +949,7 @@ void enqueue_assemble(Plan& P, double* const* cores, hipStream_t st) {
     batch.flush();
   }
   batch.flush();
-  launch_status_fold(P.d_flag, jl.n + 1, P.d_flag + kCallWord, P.d_flag + kStickyWord, st);
+  launch_status_fold(P.d_finite, list_blocks(s), P.d_flag, jl.n, P.d_flag + kCallWord, P.d_flag + kStickyWord, st);
   P.has_cores = true;
 }
 

@@ -129,7 +129,6 @@ __global__ void finite_kernel(const double* p, int64_t n, int* flag) {
 
 // Block b of a list launch serves segment `seg` (blocks are dealt to segments in
 // proportion to their length, at most kSegBlocks each).
-constexpr int kSegBlocks = 512;
 __device__ inline int seg_of(const SegList& s, int b, int* first) {
   int acc = 0;
   for (int i = 0; i < s.count; ++i) {
@@ -154,14 +153,19 @@ __global__ void zero_list_kernel(SegList s) {
   for (int64_t e = static_cast<int64_t>(blockIdx.x - first) * 256 + threadIdx.x; e < s.n[i]; e += nb * 256)
     s.p[i][e] = 0.0;
 }
+// flag[b] = whether block b met an entry that is not finite (every block's word is written,
+// so that nothing has to clear them first: a launch of its own, 4 us of a 79 us step)
 __global__ void finite_list_kernel(SegList s, int* flag) {
   int first = 0;
   const int i = seg_of(s, blockIdx.x, &first);
   if (i < 0) return;
+  int bad = 0;
   int64_t nb = (s.n[i] + 255) / 256;
   nb = nb > kSegBlocks ? kSegBlocks : (nb < 1 ? 1 : nb);
   for (int64_t e = static_cast<int64_t>(blockIdx.x - first) * 256 + threadIdx.x; e < s.n[i]; e += nb * 256)
-    if (!isfinite(s.p[i][e])) *flag = 1;
+    if (!isfinite(s.p[i][e])) bad = 1;
+  bad = __syncthreads_or(bad);
+  if (threadIdx.x == 0) flag[blockIdx.x] = bad;
 }
 
 inline bool fold_pays(int nchunks, int64_t E) { return nchunks > 2 * kFold && E < (int64_t(1) << 20); }
@@ -423,7 +427,7 @@ void launch_f64_to_f32(float* y, const double* x, int64_t n, hipStream_t st) {
 void launch_zero_int(int* p, int64_t n, hipStream_t st) {
   if (n > 0) hipLaunchKernelGGL(zero_int_kernel, dim3(grid_for(n)), dim3(256), 0, st, p, n);
 }
-static int list_blocks(const SegList& s) {
+int list_blocks(const SegList& s) {
   int64_t b = 0;
   for (int i = 0; i < s.count; ++i) {
     int64_t nb = (s.n[i] + 255) / 256;

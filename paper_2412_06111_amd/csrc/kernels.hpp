@@ -311,7 +311,11 @@ struct SegList {
   }
 };
 void launch_zero_list(const SegList& s, hipStream_t stream);
+// flag[b] for the list_blocks(s) workgroups of the launch
 void launch_finite_list(const SegList& s, int* flag, hipStream_t stream);
+// Workgroups of a list launch: one for every 256 entries of an array, kSegBlocks at most
+constexpr int kSegBlocks = 512;
+int list_blocks(const SegList& s);
 void launch_axpy(double* y, const double* x, double alpha, int64_t n, hipStream_t stream);
 void launch_copy_f64(double* dst, const double* src, int64_t n, hipStream_t stream);
 void launch_f64_to_f32(float* dst, const double* src, int64_t n, hipStream_t stream);
@@ -341,9 +345,10 @@ size_t qr_pinv_lds_bytes(int k, int r);
 // Whether a job with these k >= r fits the recovery kernel (one workgroup, its LDS);
 // plans check every node at creation.
 bool qr_pinv_fits(int k, int r);
-// Status of one assembly from its flags (flags[0] non-finite count, flags[1..nn-1] kept
-// singular values per node): *call = 1 if bad else 0, and *sticky |= *call.
-void launch_status_fold(const int* flags, int nn, int* call, int* sticky, hipStream_t stream);
+// Status of one assembly from its flags (finite[0..nf) of launch_finite_list, kept[0..nn)
+// singular values kept per node): *call = 1 if bad else 0, and *sticky |= *call.
+void launch_status_fold(const int* finite, int nf, const int* kept, int nn, int* call, int* sticky,
+                        hipStream_t stream);
 
 // ---------------------------------------------------------------- norms
 // Deterministic two-pass sums of (a - b)^2 and b^2; result in d_out[0..1].

@@ -392,6 +392,7 @@ std::unique_ptr<Plan> build_plan(const ttnn_problem* pr, hipStream_t stream, boo
   P->psi_root = static_cast<double*>(P->alloc(sizeof(double) * P->psi_root_len));
   P->d_flag = static_cast<int*>(P->alloc(sizeof(int) * 2 * TTNN_MAX_NODES));
   if (!dry) launch_zero_int(P->d_flag, 2 * TTNN_MAX_NODES, stream);     // status words start clear
+  P->d_finite = static_cast<int*>(P->alloc(sizeof(int) * kSegBlocks * (2 * P->nodes.size() + 1)));
   P->g64_part_elems = size_t(1) << 21;
   P->g64_part = static_cast<double*>(P->alloc(sizeof(double) * P->g64_part_elems));
 

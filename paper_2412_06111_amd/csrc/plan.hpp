@@ -92,7 +92,8 @@ struct Plan {
   size_t r1_w = 0;                         // g_s entries of a term (sum of k_s)
   double* work = nullptr;                  // assembly / reconstruction scratch
   size_t work_elems = 0;
-  int* d_flag = nullptr;                   // numeric-status flag written by kernels
+  int* d_flag = nullptr;                   // numeric-status words written by kernels
+  int* d_finite = nullptr;                 // the finite check's word per workgroup
   double* g64_part = nullptr;              // split-contraction scratch of the batched FP64 GEMM
   size_t g64_part_elems = 0;
 

@@ -484,12 +484,15 @@ __global__ __launch_bounds__(kThreads) void qr_pinv_kernel(QrJobList jl, double 
   }
 }
 
-// one thread: an assembly is bad if a sketch was not finite or a node kept nothing
-__global__ void status_fold_kernel(const int* __restrict__ flags, int nn, int* __restrict__ call,
-                                   int* __restrict__ sticky) {
+// one workgroup: an assembly is bad if a sketch was not finite or a node kept nothing
+__global__ __launch_bounds__(kThreads) void status_fold_kernel(const int* __restrict__ finite, int nf,
+                                                               const int* __restrict__ kept, int nn,
+                                                               int* __restrict__ call, int* __restrict__ sticky) {
+  int bad = 0;
+  for (int i = threadIdx.x; i < nf; i += kThreads) bad |= finite[i];
+  for (int v = threadIdx.x; v < nn; v += kThreads) bad |= kept[v] == 0 ? 1 : 0;
+  bad = __syncthreads_or(bad) ? 1 : 0;
   if (threadIdx.x != 0) return;
-  int bad = flags[0] != 0 ? 1 : 0;
-  for (int v = 1; v < nn; ++v) bad |= flags[v] == 0 ? 1 : 0;
   *call = bad;
   *sticky = *sticky | bad;
 }
@@ -567,8 +570,8 @@ void launch_qr_pinv(const QrJobList& jl, double eps_factor, int* d_kept, hipStre
   launch(reinterpret_cast<const void*>(qr_pinv_kernel<24>), 2, qr_pinv_kernel<24>);
 }
 
-void launch_status_fold(const int* flags, int nn, int* call, int* sticky, hipStream_t st) {
-  hipLaunchKernelGGL(status_fold_kernel, dim3(1), dim3(64), 0, st, flags, nn, call, sticky);
+void launch_status_fold(const int* finite, int nf, const int* kept, int nn, int* call, int* sticky, hipStream_t st) {
+  hipLaunchKernelGGL(status_fold_kernel, dim3(1), dim3(kThreads), 0, st, finite, nf, kept, nn, call, sticky);
 }
 
 void launch_diff_norms(const void* a, int a_dtype, const double* b, int64_t n, double* d_part, double* d_out,
