@@ -27,8 +27,9 @@ namespace ttnn {
 // wave issues ~60 vector instructions beside the 16 MFMAs of a 64 x 32 x 32 step, and the
 // tile is bound by those two and the barrier between steps (MFMA busy 32%).  Measured
 // with it before and now: a whole 97 x 113 x 61 x 75 FP32 tensor (r = 21, TTNN) 1250 ->
-// 610 us (a pass over the 200 MB 140-220 -> 62-98 us); a 33.9M-entry box of a 64^5 FP32
-// tensor (r = 24) 1764 -> 795 us; two steps of loads in flight changed nothing.
+// 500 us (a pass over the 200 MB 140-220 -> 55-90 us); a 33.9M-entry box of a 64^5 FP32
+// tensor (r = 24) 1764 -> 686 us, the faster packing included; two steps of loads in flight
+// at three workgroups a compute unit 519 and 685, at four (spilling) 525 and 718.
 //
 // Products run on the 16x16x4 MFMA of the compute type CT: FP64 when an operand is FP64,
 // else FP32 with the running sums moved to FP64 registers every kFlush steps, so a
@@ -82,6 +83,14 @@ __device__ inline void split_at(int64_t idx, int64_t L, int64_t& a, int64_t& b) 
   }
 }
 
+// A task's pointers come out of LDS, where the compiler cannot see that they are global: its
+// flat loads count as LDS reads too, and every wait for an LDS operand would wait for them.
+#define TTNN_GLOBAL __attribute__((address_space(1)))
+typedef const char TTNN_GLOBAL* GlobalPtr;
+template <typename T> __device__ __forceinline__ T load_global(GlobalPtr p) {
+  return *reinterpret_cast<const T TTNN_GLOBAL*>(p);
+}
+
 template <typename CT> __device__ inline CT to_ct(float v) { return static_cast<CT>(v); }
 template <typename CT> __device__ inline CT to_ct(double v) { return static_cast<CT>(v); }
 template <typename CT> __device__ inline CT to_ct(uint16_t v) { return static_cast<CT>(bf16_bits_to_f32(v)); }
@@ -95,11 +104,12 @@ __device__ __forceinline__ void gemm_tile(const GemmTask& t, int64_t row0, int64
   constexpr int V = Dm::V, BKX = Dm::BKX, PITCH = Dm::PITCH, KW = Dm::KW, NJ = 16 * NCB;
   constexpr int KG = 4 * V;                       // contraction values per fragment read
   constexpr int NA = TR * BKX / 256;              // operand entries a thread stages per step
-  constexpr int RS = 256 / BKX;                   // contraction along memory: rows apart of a thread's entries
+  constexpr int GK = BKX / V;                     // groups of V contraction values of a step
+  constexpr int RS = 256 / GK;                    // contraction along memory: rows apart of a thread's groups
   constexpr int RW = TR < 32 ? TR : 32;           // rows along memory: rows per pass ...
-  constexpr int KS = 256 / RW, NK = BKX / KS;     // ... and values apart, values of a pass
+  constexpr int KS = V * 256 / RW, NK = BKX / KS; // ... and values apart of its groups, groups of a row
   constexpr int NBK = BKX / 16;                   // DRM rows a thread stages per step
-  static_assert(NA == NK * (TR / RW) && BKX <= kTab && kTab % BKX == 0 && 256 % BKX == 0, "tile shape");
+  static_assert(NA == V * NK * (TR / RW) && NA == V * (TR / RS) && BKX <= kTab && kTab % BKX == 0 && 256 % BKX == 0, "tile shape");
   typedef CT vec_t __attribute__((ext_vector_type(V)));
 
   CT* As = reinterpret_cast<CT*>(lds);            // [2][TR][PITCH]
@@ -152,24 +162,30 @@ __device__ __forceinline__ void gemm_tile(const GemmTask& t, int64_t row0, int64
   fill(0, k_begin);
   __syncthreads();
 
-  // staging map of a thread: contraction along memory, value kk0 of rows rr0 + RS s; rows
-  // along memory, values kk0 + KS u of rows rr0 + RW b
-  const int kk0 = kfast ? tid % BKX : tid / RW;
-  const int rr0 = kfast ? tid / BKX : tid % RW;
+  // Staging map of a thread, which takes groups of V consecutive contraction values of a row
+  // (one 16-byte LDS store each): contraction along memory, group kk0 of rows rr0 + RS s;
+  // rows along memory, groups kk0 + KS u of rows rr0 + RW b.  Along memory a group inside one
+  // run of it is one load (of any alignment).  With single values, a load and a 4-byte store
+  // each, and flat loads the whole 97 x 113 x 61 x 75 FP32 tensor took 549 us, with single
+  // values and global loads 517, now 500 (the 33.9M-entry box 727, 686, 686).
+  const int kk0 = V * (kfast ? tid % GK : tid / RW);
+  const int rr0 = kfast ? tid / GK : tid % RW;
+  const bool runs = !t.hm.strided;
   // Rows past the end read row 0 of the operand and columns past the end column j0 of the
   // DRM: what they form lands in rows and columns that are not written.
-  const char* hp[NA];
+  constexpr int NR = TR / RS > TR / RW ? TR / RS : TR / RW;    // rows of a thread
+  GlobalPtr hp[NR];
 #pragma unroll
-  for (int s = 0; s < NA; ++s) {
-    const int64_t o = rows[kfast ? rr0 + RS * s : rr0 + RW * (s % (TR / RW))];
-    hp[s] = static_cast<const char*>(t.H) + (o < 0 ? 0 : o) * static_cast<int64_t>(sizeof(TH));
+  for (int s = 0; s < NR; ++s) {
+    const int64_t o = rows[(kfast ? rr0 + RS * s : rr0 + RW * s) % TR];
+    hp[s] = (GlobalPtr)t.H + (o < 0 ? 0 : o) * static_cast<int64_t>(sizeof(TH));
   }
   const int jl = tid & 15, kb0 = tid >> 4;
-  const char* dp[NCB];
+  GlobalPtr dp[NCB];
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
     const int col = j0 + 16 * cb + jl < ncols ? j0 + 16 * cb + jl : j0;
-    dp[cb] = static_cast<const char*>(t.D) + col * t.sDc * static_cast<int64_t>(sizeof(TD));
+    dp[cb] = (GlobalPtr)t.D + col * t.sDc * static_cast<int64_t>(sizeof(TD));
   }
 
   // A step's loads, and its stores to LDS.  Values past the end of the chunk read value 0
@@ -186,21 +202,37 @@ __device__ __forceinline__ void gemm_tile(const GemmTask& t, int64_t row0, int64
     const TileOff* tp = tab + static_cast<int>((k0 - k_begin) & (2 * kTab - 1));
     if (kfast) {
       const int64_t h = tp[kk0].h;
+      if (runs && tp[kk0 + V - 1].h - h == static_cast<int64_t>((V - 1) * sizeof(TH))) {
+        typedef TH group_t __attribute__((ext_vector_type(V), aligned(sizeof(TH))));
 #pragma unroll
-      for (int s = 0; s < NA; ++s) g.a[s] = *reinterpret_cast<const TH*>(hp[s] + h);
+        for (int s = 0; s < TR / RS; ++s) {
+          const group_t q = load_global<group_t>(hp[s] + h);
+#pragma unroll
+          for (int v = 0; v < V; ++v) g.a[s * V + v] = q[v];
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const int64_t hv = tp[kk0 + v].h;
+#pragma unroll
+          for (int s = 0; s < TR / RS; ++s) g.a[s * V + v] = load_global<TH>(hp[s] + hv);
+        }
+      }
     } else {
 #pragma unroll
-      for (int u = 0; u < NK; ++u) {
-        const int64_t h = tp[kk0 + KS * u].h;
+      for (int u = 0; u < NK; ++u)
 #pragma unroll
-        for (int b = 0; b < TR / RW; ++b) g.a[b * NK + u] = *reinterpret_cast<const TH*>(hp[b] + h);
-      }
+        for (int v = 0; v < V; ++v) {
+          const int64_t h = tp[kk0 + KS * u + v].h;
+#pragma unroll
+          for (int b = 0; b < TR / RW; ++b) g.a[(b * NK + u) * V + v] = load_global<TH>(hp[b] + h);
+        }
     }
 #pragma unroll
     for (int u = 0; u < NBK; ++u) {
       const int64_t d = tp[kb0 + 16 * u].d;
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) g.b[u * NCB + cb] = *reinterpret_cast<const TD*>(dp[cb] + d);
+      for (int cb = 0; cb < NCB; ++cb) g.b[u * NCB + cb] = load_global<TD>(dp[cb] + d);
     }
   };
   // LAST: only the first klen values of the step exist
@@ -208,15 +240,20 @@ __device__ __forceinline__ void gemm_tile(const GemmTask& t, int64_t row0, int64
     constexpr bool LAST = decltype(last)::value;
     CT* A = As + buf * TR * PITCH + rr0 * PITCH + kk0;
     CT* B = Bs + buf * NJ * PITCH + jl * PITCH + kb0;
+    auto put = [&](CT* to, const TH* x, int k) {
+      vec_t w;
+#pragma unroll
+      for (int v = 0; v < V; ++v) w[v] = !LAST || k + v < klen ? to_ct<CT>(x[v]) : CT(0);
+      *reinterpret_cast<vec_t*>(to) = w;
+    };
     if (kfast) {
 #pragma unroll
-      for (int s = 0; s < NA; ++s) A[RS * s * PITCH] = !LAST || kk0 < klen ? to_ct<CT>(g.a[s]) : CT(0);
+      for (int s = 0; s < TR / RS; ++s) put(A + RS * s * PITCH, &g.a[s * V], kk0);
     } else {
 #pragma unroll
       for (int b = 0; b < TR / RW; ++b)
 #pragma unroll
-        for (int u = 0; u < NK; ++u)
-          A[RW * b * PITCH + KS * u] = !LAST || kk0 + KS * u < klen ? to_ct<CT>(g.a[b * NK + u]) : CT(0);
+        for (int u = 0; u < NK; ++u) put(A + RW * b * PITCH + KS * u, &g.a[(b * NK + u) * V], kk0 + KS * u);
     }
 #pragma unroll
     for (int u = 0; u < NBK; ++u)
@@ -294,7 +331,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTask& t, int64_t row0, int64
   }
 
   // lane holds C[16 wr + crow(lane, v)][16 cb + l16]
-  double* __restrict__ out = static_cast<double*>(t.out) + c * t.ol.cs;
+  double TTNN_GLOBAL* out = (double TTNN_GLOBAL*)t.out + c * t.ol.cs;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int64_t row = row0 + 16 * wr + P::crow(lane, v);

@@ -81,3 +81,29 @@ def test_reconstruct_edges(dims, r, out):
     err = np.linalg.norm(got.double().cpu().numpy() - want.ravel(order="F")) / np.linalg.norm(want)
     assert err < (1e-12 if out == "f64" else 1e-7), err       # FP64 sums; FP32: one rounding of the result
     plan.close()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("ext", [(2, 37, 19), (3, 18, 40), (4, 50, 9), (5, 33, 21), (7, 16, 30), (33, 65, 5)], ids=str)
+def test_tile_groups_across_runs(ext, dtype):
+    """Contractions along memory whose runs (mode 1) are shorter than, as long as and no
+    multiple of a thread's group of values, on blocks that start one entry past an aligned
+    address, packed and read in place in another order of modes."""
+    import paper_2412_06111_amd as P
+    spec, dims, off = ((1, 2), 3), tuple(e + 1 for e in ext), (1, 0, 1)
+    g = np.random.default_rng(sum(ext))
+    dev, consumed = to_device(g.standard_normal(ext), dtype)
+    shifted = torch.empty(dev.numel() + 1, dtype=dev.dtype, device="cuda")[1:]
+    shifted.copy_(dev)
+    swapped = dev.view(*reversed(ext)).transpose(0, 2).contiguous().transpose(0, 2)   # mode 3 fastest in memory
+    full = np.zeros(dims)
+    full[1:, :-1, 1:] = consumed
+    tree = O.Tree(spec, dims, 9, 4)
+    sk = O.sketch(full, tree, O.DRMs(tree, 5, "ttnn", dtype), "ttnn")
+    for block in (shifted, swapped):
+        plan = P.Plan(spec, dims, 9, 4, variant="ttnn", dtype=dtype, seed=5)
+        plan.update(block, extent=ext, offset=off)
+        torch.cuda.synchronize()
+        errs = sketch_errors(plan, tree, sk)
+        assert not failures(errs, TOL_ARITH[dtype]), errs
+        plan.close()
