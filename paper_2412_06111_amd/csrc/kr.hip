@@ -9,19 +9,27 @@
 // gives the down vectors of a node; with the siblings' and the parent's vectors, the up
 // vectors of a child.  Split the reduction index into the first non-output axis a
 // (size n0) and the rest e (the outer combinations):
-//   out[o, j] = sum_e w_e[j] sum_a C_e[o, a] F_0[a, j],  w_e[j] = prod_{q>=1} F_q[e_q, j],
-// one contraction over (a, e) whose right operand F_0[a, j] w_e[j] is formed in registers.
-// It runs on the FP64 MFMA, operands straight from global memory (a core is read once, the
-// factors stay in the caches): a wave takes 32 values of o (two row blocks) by up to 64
-// columns and a contiguous slice of the steps, four values of a of one combination each,
-// loading four steps ahead.  The four waves of a workgroup take neighbouring slices and add
-// their sums in wave order through LDS; the steps are cut into 4 G slices, and for G > 1 a
-// second kernel adds the G partials in a fixed order, so the result depends only on the
-// shapes.
+//   out[o, j] = sum_e w_e[j] sum_a C_e[o, a] F_0[a, j],  w_e[j] = prod_{q>=1} F_q[e_q, j].
+//
+// The order of the sums is part of what the kernel promises: the cores of a rounding are
+// R Omega^+ with an Omega that the ranks' decay leaves ill conditioned, and summing in
+// another order moves them by up to 2e-9 (a two-child root, ranks decaying as 1 / i^2, r =
+// 28).  A unit is one outer combination e and one chunk of at most 32 values of a (the chunks
+// of equal length); its t = sum_a C F_0 is a chain of fused multiply-adds in the order of a,
+// and out the chain out = fma(w_e, t, out) in the order of the units.  The units are cut into
+// G contiguous slices, one workgroup each, whose results a second kernel adds in order.
+//
+// The chains over a run on the FP64 MFMA, which adds its four products one after the other by
+// fused multiply-adds in the order of the contraction index, operands straight from global
+// memory (a core is read once, the factors stay in the caches): a wave takes one unit of 32
+// values of o (two row blocks) by up to 64 columns, the eight waves of a workgroup
+// neighbouring units (a slice of 70^3 cores has seven), and after each round its threads, a
+// share of the results each, add the t in order.
 //
 // Bound by latency: the six 70^3 cores of a 500^6 tensor's tree are 1 to 4 us of MFMA work a
-// level.  A level took 24-30 us on FP64 VALU products of LDS tiles (seven serial units of a
-// load, a barrier and 24 steps); now 10-17.
+// level.  A level's launch takes 7 to 25 us, 14 on average; with FP64 VALU products of LDS
+// tiles, seven serial units of a load, a barrier and 24 steps, it took 24-30 (the rounding
+// 303 us, now 242).
 #include "kr.hpp"
 
 #include <algorithm>
@@ -32,11 +40,19 @@ namespace ttnn {
 
 namespace {
 
-constexpr int kTO = 32, kTJ = 64;          // values of o and columns (at most) of a workgroup
-constexpr int kAhead = 4;                  // steps of loads in flight
+constexpr int kTO = 32, kTJ = 64, kKC = 32;   // values of o, columns (at most), of a (at most) of a unit
+constexpr int kAhead = 4;                     // steps of four values of a loaded together
+constexpr int kUnits = 8;                     // units of a round: waves of a workgroup
+
+// Chunks of the inner axis: as few as hold n0 in chunks of at most kKC, of equal length.
+__host__ __device__ inline int64_t kr_nchunks(int64_t n0) { return (n0 + kKC - 1) / kKC; }
+__host__ __device__ inline int kr_chunk(int64_t n0) {
+  const int64_t nch = kr_nchunks(n0);
+  return static_cast<int>((n0 + nch - 1) / nch);
+}
 
 template <int NCB>
-__global__ __launch_bounds__(256) void kr_contract_kernel(KJobList) {
+__global__ __launch_bounds__(64 * kUnits) void kr_contract_kernel(KJobList) {
   using P = Pol<TTNN_F64>;
   // the job's fields by scalar loads (indexing a by-value argument would copy it to scratch)
   typedef const KJobList __attribute__((address_space(4))) ConstList;
@@ -62,11 +78,10 @@ __global__ __launch_bounds__(256) void kr_contract_kernel(KJobList) {
   int64_t so_stride = 1;
   for (int q = 0; q < oax; ++q) so_stride *= J.size[q];
   const int64_t st0 = in == 0 ? 1 : so;
-  const int64_t nst = (n0 + 3) / 4, steps = J.kred / n0 * nst;
-  const int64_t slice = 4 * g + wave;
-  const int64_t hi = steps * (slice + 1) / (4 * J.G);
-  int64_t at = steps * slice / (4 * J.G);    // the next step to load: values 4 t.. of combination e
-  int64_t e = at / nst, t = at - e * nst;
+  const int64_t nch = kr_nchunks(n0);
+  const int kc = kr_chunk(n0);
+  const int64_t units = J.kred / n0 * nch;
+  const int64_t ulo = units * g / J.G, uhi = units * (g + 1) / J.G;
 
   // Rows past the end read the last row and columns past the end the last column: what they
   // form is not delivered.
@@ -80,21 +95,20 @@ __global__ __launch_bounds__(256) void kr_contract_kernel(KJobList) {
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) jc[cb] = j0 + 16 * cb + l16 < cols ? j0 + 16 * cb + l16 : cols - 1;
 
-  // Up to kAhead steps of one combination: operands and, per column, the other axes' product
-  struct Block {
-    double a[2][kAhead], f[NCB][kAhead], w[NCB];
-    int n;                                   // steps in it
-    int64_t last;                            // values of a from its first on
-  };
-  auto fetch = [&](Block& k) {
-    k.n = 0;
-    if (at >= hi) return;
-    int64_t n = nst - t < hi - at ? nst - t : hi - at;
-    k.n = static_cast<int>(n < kAhead ? n : kAhead);
-    k.last = n0 - 4 * t;
-    int64_t off = 0, rest = e, stride = 1;
+  // The unit being loaded: its values of a, core offset and column weights
+  int run = 0;
+  int64_t a0 = 0, off = 0;
+  double w[NCB];
+  auto open = [&](int64_t u) {
+    run = 0;
+    if (u >= uhi) return;
+    const int64_t e = u / nch;
+    a0 = (u - e * nch) * kc;
+    run = static_cast<int>(n0 - a0 < kc ? n0 - a0 : kc);
+    off = 0;
+    int64_t rest = e, stride = 1;
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) k.w[cb] = 1.0;
+    for (int cb = 0; cb < NCB; ++cb) w[cb] = 1.0;
     for (int q = 0; q < naxes; ++q) {
       const int64_t sz = J.size[q];
       if (q != oax && q != in) {
@@ -103,78 +117,98 @@ __global__ __launch_bounds__(256) void kr_contract_kernel(KJobList) {
         off += d * stride;
         const double* F = J.fac[q] + d * cols;
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) k.w[cb] *= F[jc[cb]];
+        for (int cb = 0; cb < NCB; ++cb) w[cb] *= F[jc[cb]];
       }
       stride *= sz;
     }
+  };
+  // Half of a unit: kAhead steps of four values of a from 4 kAhead H on
+  struct Half {
+    double a[2][kAhead], f[NCB][kAhead];
+  };
+  static_assert(kKC == 8 * kAhead, "two halves a unit");
+  auto fetch = [&](Half& k, int h) {
+    if (4 * kAhead * h >= run) return;
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      // past the block or past n0: the first value, zeroed before its product
-      const int64_t v = 4 * (t + u) + lg, a = u < k.n && v < n0 ? v : 0;
+    for (int s = 0; s < kAhead; ++s) {
+      // past the unit's values: its first one, zeroed before its product
+      const int v = 4 * (kAhead * h + s) + lg;
+      const int64_t a = a0 + (v < run ? v : 0);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) k.a[i][u] = row[i][off + a * st0];
+      for (int i = 0; i < 2; ++i) k.a[i][s] = row[i][off + a * st0];
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) k.f[cb][u] = F0 ? F0[a * cols + jc[cb]] : 1.0;
-    }
-    at += k.n;
-    t += k.n;
-    if (t == nst) {
-      t = 0;
-      ++e;
+      for (int cb = 0; cb < NCB; ++cb) k.f[cb][s] = F0 ? F0[a * cols + jc[cb]] : 1.0;
     }
   };
-  f64x4_t acc[2][NCB];
+  f64x4_t t[2][NCB];
+  auto products = [&](const Half& k, int h, int n) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) acc[i][cb] = f64x4_t{0.0, 0.0, 0.0, 0.0};
-  auto products = [&](const Block& k) {
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      if (u >= k.n) break;
-      const bool live = 4 * u + lg < k.last;
+    for (int s = 0; s < kAhead; ++s) {
+      const int at = 4 * (kAhead * h + s);
+      if (at >= n) break;
+      const bool live = at + lg < n;
       double x[2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) x[i] = live ? k.a[i][u] : 0.0;
+      for (int i = 0; i < 2; ++i) x[i] = live ? k.a[i][s] : 0.0;
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
         if (j0 + 16 * cb >= cols) continue;
-        const double y = live ? k.f[cb][u] * k.w[cb] : 0.0;
+        const double y = live ? k.f[cb][s] : 0.0;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) acc[i][cb] = P::mfma(x[i], y, acc[i][cb]);
+        for (int i = 0; i < 2; ++i) t[i][cb] = P::mfma(x[i], y, t[i][cb]);
       }
     }
   };
-  Block k0, k1;
-  fetch(k0);
-  while (k0.n) {
-    fetch(k1);
-    products(k0);
-    if (!k1.n) break;
-    fetch(k0);
-    products(k1);
-  }
 
-  // the four waves' sums, added in wave order
-  __shared__ double red[4][8][64];
-  for (int cb = 0; cb < NCB; ++cb) {
+  // [wave][result register][lane] and [wave][column]: the units of a round and their weights.
+  // A thread adds up register `wave` of the eight of its lane's row blocks.
+  __shared__ double red[kUnits][8 * NCB][64];
+  __shared__ double wl[kUnits][16 * NCB];
+  static_assert(kUnits == 8, "a register of each column block a wave");
+  double acc[NCB];
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb) acc[cb] = 0.0;
+  Half k0, k1;
+  open(ulo + wave);
+  fetch(k0, 0);
+  fetch(k1, 1);
+  for (int64_t u0 = ulo; u0 < uhi; u0 += kUnits) {
+    const int n = run;                       // of this round's unit; 0: none
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) red[wave][4 * i + v][lane] = acc[i][cb][v];
-    __syncthreads();
+      for (int cb = 0; cb < NCB; ++cb) t[i][cb] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+    if (lg == 0) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int x = wave + 4 * h;            // row block x / 4, result x % 4 of this lane
-      const double sum = red[0][x][lane] + red[1][x][lane] + red[2][x][lane] + red[3][x][lane];
-      const int64_t o = o0 + 16 * (x / 4) + P::crow(lane, x % 4);
-      const int64_t j = j0 + 16 * cb + l16;
-      if (o < so && j < cols) {
-        if (J.G == 1) J.out[o * cols + j] = sum;
-        else J.part[(g * so + o) * cols + j] = sum;
-      }
+      for (int cb = 0; cb < NCB; ++cb) wl[wave][16 * cb + l16] = w[cb];
     }
+    open(u0 + kUnits + wave);                // the next round's loads go out behind the products
+    products(k0, 0, n);
+    fetch(k0, 0);
+    products(k1, 1, n);
+    fetch(k1, 1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[wave][(2 * cb + i) * 4 + v][lane] = t[i][cb][v];
     __syncthreads();
+    const int nu = static_cast<int>(uhi - u0 < kUnits ? uhi - u0 : kUnits);
+    for (int u = 0; u < nu; ++u)
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb)
+        acc[cb] = fma(wl[u][16 * cb + l16], red[u][8 * cb + wave][lane], acc[cb]);
+    __syncthreads();
+  }
+  const int64_t o = o0 + 16 * (wave / 4) + P::crow(lane, wave % 4);
+#pragma unroll
+  for (int cb = 0; cb < NCB; ++cb) {
+    const int64_t j = j0 + 16 * cb + l16;
+    if (o < so && j < cols) {
+      if (J.G == 1) J.out[o * cols + j] = acc[cb];
+      else J.part[(g * so + o) * cols + j] = acc[cb];
+    }
   }
 }
 
@@ -207,9 +241,9 @@ __global__ __launch_bounds__(256) void kr_fold_kernel(KJobList L) {
 
 int kr_split(int64_t so, int cols, int64_t n0, int64_t nouter) {
   const int64_t tiles = ((so + kTO - 1) / kTO) * ((cols + kTJ - 1) / kTJ);
-  const int64_t steps = nouter * ((n0 + 3) / 4);
+  const int64_t units = nouter * kr_nchunks(n0);
   int64_t G = tiles >= 512 ? 1 : 512 / tiles;
-  if (G > steps / 32) G = steps / 32;                  // at least eight steps a wave
+  if (G > units / 2) G = units / 2;                    // at least two units per slice
   if (G > 32) G = 32;                                  // the fold reads G partials per output
   return G < 1 ? 1 : static_cast<int>(G);
 }
@@ -245,10 +279,10 @@ void launch_kr_contract(std::vector<KJob> jobs, hipStream_t stream) {
     }
     const dim3 grid(static_cast<unsigned>(blocks));
     if (blocks > 0) {
-      if (width == 1) kr_contract_kernel<1><<<grid, dim3(256), 0, stream>>>(L);
-      else if (width == 2) kr_contract_kernel<2><<<grid, dim3(256), 0, stream>>>(L);
-      else if (width == 3) kr_contract_kernel<3><<<grid, dim3(256), 0, stream>>>(L);
-      else kr_contract_kernel<4><<<grid, dim3(256), 0, stream>>>(L);
+      if (width == 1) kr_contract_kernel<1><<<grid, dim3(64 * kUnits), 0, stream>>>(L);
+      else if (width == 2) kr_contract_kernel<2><<<grid, dim3(64 * kUnits), 0, stream>>>(L);
+      else if (width == 3) kr_contract_kernel<3><<<grid, dim3(64 * kUnits), 0, stream>>>(L);
+      else kr_contract_kernel<4><<<grid, dim3(64 * kUnits), 0, stream>>>(L);
     }
     if (fblocks > 0) kr_fold_kernel<<<dim3(static_cast<unsigned>(fblocks)), dim3(256), 0, stream>>>(L);
   }

@@ -207,3 +207,51 @@ def test_contraction_tile_edges(P, s, r, p):
     bad = failures(sketch_errors(plan, tree, S.ttn_sketch(cores, tree, X, Y)), TOL["f64"])
     assert not bad, bad
     plan.close()
+
+
+def _fma(a, b, c):
+    """a b + c rounded once (a quotient of integers converts to the nearest double)."""
+    (an, ad), (bn, bd), (cn, cd) = (float(x).as_integer_ratio() for x in (a, b, c))
+    return (an * bn * cd + cn * ad * bd) / (ad * bd * cd)
+
+
+def _contracted_in_order(core, F, axes, cols, o, j):
+    """Entry (o, j) of the contraction of core[o, a, b] (o first) with F[0][a, j] and F[1][b,
+    j]: the sum that the library promises.  Chunks of at most 32 values of a, of equal length;
+    t a chain of fused multiply-adds over a chunk, the chunks' t chained likewise with the
+    weight F[1][b, j]; the units (chunks within b) in G slices whose sums are added in order."""
+    so, n0, nb = axes
+    nch = -(-n0 // 32)
+    kc, units = -(-n0 // nch), nb * nch
+    G = max(1, min(512 // (-(-so // 32) * -(-cols // 64)), units // 2, 32))
+    total = 0.0
+    for g in range(G):
+        acc = 0.0
+        for u in range(units * g // G, units * (g + 1) // G):
+            b, a0 = u // nch, u % nch * kc
+            t = 0.0
+            for a in range(a0, min(a0 + kc, n0)):
+                t = _fma(core[o, a, b], F[0][a, j], t)
+            acc = _fma(F[1][b, j], t, acc)
+        total += acc
+    return total
+
+
+@pytest.mark.parametrize("s,r", [(5, 3), (31, 16), (33, 20), (70, 64)])
+def test_contraction_order(P, s, r):
+    """The tree contractions' sums in their promised order, bit for bit (a rounding's cores
+    magnify another order's rounding errors by the conditioning of Omega).  With identity
+    leaves the children's vectors are the factors themselves, and R of the first leaf is its
+    up vector, one contraction of the root's core."""
+    dims, p = (s,) * 3, 2
+    rng = np.random.default_rng(s)
+    core = rng.standard_normal((s, s, s))
+    X, _ = S.factors(9, dims, r, p)
+    plan = P.Plan((1, 2, 3), dims, r, p, variant="kr", seed=9)
+    eye = np.eye(s)
+    plan.update_ttn(dev_cores({(1,): eye, (2,): eye, (3,): eye, (1, 2, 3): core}), s)
+    got = plan.read_sketch(plan.node_of_modes[(1,)], P.SK_R).cpu().numpy()
+    for o in sorted({0, s // 2, s - 1}):
+        for j in sorted({0, r // 2, r - 1}):
+            assert got[o, j] == _contracted_in_order(core, (X[1], X[2]), (s, s, s), r, o, j), (o, j)
+    plan.close()
