@@ -215,18 +215,30 @@ __global__ __launch_bounds__(256) void bgemm64_combine_kernel(GJobList L) {
 // with masked edges and 64-byte stores 420, now 315 (MFMA busy 78%; 17.2 GFLOP take 239 us
 // at the rate of a large FP64 product).
 // SMALL (M < 64 or N < 32): rows past the end read the last one and are not written.
+//
+// A workgroup's waves are wl along l by 4 / wl along j, XCDs xl along l by 8 / xl along j
+// (OuterSplit): with the one fixed split, 2 x 2 waves and all XCDs along l, M <= 128 left
+// seven of the eight XCDs idle.
+struct OuterSplit {
+  int wl, xl;
+  uint32_t lx, jx;               // tiles of an XCD along l and j
+};
 template <typename TO, bool SMALL>
 __global__ __launch_bounds__(256, 4) void outer64_kernel(const double* __restrict__ A, const double* __restrict__ B,
-                                                         int64_t M, int64_t N, int K, TO* __restrict__ out) {
+                                                         int64_t M, int64_t N, int K, OuterSplit sp,
+                                                         TO* __restrict__ out) {
   // results of 16 rows of B by 64 of A; the pitch puts the lane groups' rows 16 banks apart
   __shared__ TO tile[4][16][80];
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // workgroups go to the XCDs in turn: XCD x takes the x-th eighth of the l tiles (its part
-  // of A stays in its cache) and walks the j tiles
-  const uint32_t lx = static_cast<uint32_t>((M + 1023) / 1024), rel = blockIdx.x / 8;
-  int64_t l0 = (static_cast<int64_t>(blockIdx.x % 8) * lx + rel % lx) * 128 + 64 * (wave & 1);
-  int64_t j0 = static_cast<int64_t>(rel / lx) * 64 + 32 * (wave >> 1);
+  // workgroups go to the XCDs in turn: XCD x takes part x % xl of the l tiles (its part of A
+  // stays in its cache) and part x / xl of the j tiles, and walks them l first
+  const int x = blockIdx.x % 8;
+  const uint32_t rel = blockIdx.x / 8;
+  const int64_t lt = static_cast<int64_t>(x % sp.xl) * sp.lx + rel % sp.lx;
+  const int64_t jt = static_cast<int64_t>(x / sp.xl) * sp.jx + rel / sp.lx;
+  int64_t l0 = (lt * sp.wl + wave % sp.wl) * 64;
+  int64_t j0 = (jt * (4 / sp.wl) + wave / sp.wl) * 32;
   if (l0 >= M || j0 >= N) return;                 // no barrier follows
   if (!SMALL) {
     if (l0 > M - 64) l0 = M - 64;
@@ -339,12 +351,27 @@ void launch_bgemm64(std::vector<GJob>& jobs, double* part, size_t part_elems, hi
 void launch_outer64(const double* A, const double* B, int64_t M, int64_t N, int K, void* out, bool f32,
                     hipStream_t st) {
   if (M <= 0 || N <= 0) return;
-  const int64_t tiles = 8 * ((M + 1023) / 1024) * ((N + 63) / 64);
+  // Waves: 2 x 2 of 64 x 32 results, or all four along the other side where one side is no
+  // more than a wave's.  XCDs: all along l while that leaves none with more than an eighth
+  // over the evenest split's share of tiles (M = 16,384: 16 l tiles each), else fewer.
+  // FP32 results, the whole reconstruction, with 2 x 2 waves and all XCDs along l and now: M =
+  // 97, N = 2^20 (K = 32) 1386 -> 414 us, 128, 2^20 1352 -> 398, 500, 2^18 352 -> 290, 33,
+  // 810,000 (K = 16) 500 -> 136, 8, 9e6 (K = 8) 3817 -> 761; 16,384 x 16,384 350 both.
+  OuterSplit sp{};
+  sp.wl = M <= 64 ? 1 : N <= 32 ? 4 : 2;
+  const int64_t lts = (M + 64 * sp.wl - 1) / (64 * sp.wl), jts = (N + 128 / sp.wl - 1) / (128 / sp.wl);
+  auto share = [&](int xl) { return (lts + xl - 1) / xl * ((jts * xl + 7) / 8); };
+  int64_t least = share(8);
+  for (int xl = 4; xl > 0; xl /= 2) least = std::min(least, share(xl));
+  for (sp.xl = 8; 8 * share(sp.xl) > 9 * least; sp.xl /= 2) {}
+  const int64_t lx = (lts + sp.xl - 1) / sp.xl, jx = (jts * sp.xl + 7) / 8, tiles = 8 * lx * jx;
   TTNN_REQUIRE(tiles < (int64_t(1) << 31), TTNN_E_INVALID, "reconstruction too large for one launch");
+  sp.lx = static_cast<uint32_t>(lx);
+  sp.jx = static_cast<uint32_t>(jx);
   const dim3 grid(static_cast<unsigned>(tiles));
   auto go = [&](auto o, auto small) {
     using TO = decltype(o);
-    hipLaunchKernelGGL((outer64_kernel<TO, decltype(small)::value>), grid, dim3(256), 0, st, A, B, M, N, K,
+    hipLaunchKernelGGL((outer64_kernel<TO, decltype(small)::value>), grid, dim3(256), 0, st, A, B, M, N, K, sp,
                        static_cast<TO*>(out));
   };
   const bool small = M < 64 || N < 32;

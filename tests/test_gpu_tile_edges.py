@@ -83,6 +83,56 @@ def test_reconstruct_edges(dims, r, out):
     plan.close()
 
 
+def reconstruction(spec, dims, r, out):
+    """A plan, random cores on the device and the oracle's tensor of them."""
+    import paper_2412_06111_amd as P
+    tree = O.Tree(spec, dims, r, 0)
+    g = np.random.default_rng(sum(dims) + r)
+    cores = {n.id: g.standard_normal(O.core_shape(tree, n.id)) for n in tree.nodes}
+    plan = P.Plan(spec, dims, r, 0, variant="ttnn", dtype="f64", seed=1)
+    dev = [None] * plan.num_nodes
+    for n in tree.nodes:
+        dev[plan.node(n.modes)] = torch.from_numpy(cores[n.id].ravel(order="F").copy()).cuda()
+    return plan, dev, P.F32 if out == "f32" else P.F64, tree, cores
+
+
+@pytest.mark.parametrize("out", ["f64", "f32"])
+@pytest.mark.parametrize("dims", [(3, 23, 40), (16, 40, 50), (64, 33, 9), (65, 5, 6), (129, 30, 31), (1100, 8, 9), (1100, 5, 5)], ids=str)
+def test_reconstruct_splits(dims, out):
+    """The last step's splits over waves and XCDs: first halves from below one wave's rows to
+    several tiles an XCD, second halves from one tile on."""
+    plan, dev, kind, tree, cores = reconstruction((1, (2, 3)), dims, 3, out)
+    want = O.reconstruct({i: c.ravel(order="F") if i == 0 else c for i, c in cores.items()}, tree)
+    got = plan.reconstruct(dev, out_dtype=kind)
+    torch.cuda.synchronize()
+    err = np.linalg.norm(got.double().cpu().numpy() - want.ravel(order="F")) / np.linalg.norm(want)
+    assert err < (1e-12 if out == "f64" else 1e-7), err       # FP64 sums; FP32: one rounding of the result
+    plan.close()
+
+
+def test_reconstruct_time_either_way_round():
+    """A tensor whose first half is one mode takes about what the same entries take from even
+    halves (the last step's work is the same; with the XCDs split along the first half only it
+    took 348 us for 78).  Three times: the forming of the larger half is in it as well."""
+    us = {}
+    for spec, dims in (((1, (2, 3)), (128, 512, 512)), (((1, 2), (3, 4)), (64, 64, 64, 128))):
+        plan, dev, kind, _, _ = reconstruction(spec, dims, 32, "f32")
+        out = torch.empty(int(np.prod(dims)), dtype=torch.float32, device="cuda")
+        best = float("inf")
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                plan.reconstruct(dev, out=out, out_dtype=kind)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 200)
+        us[spec] = best
+        plan.close()
+    a, b = us.values()
+    assert a < 3 * b, us
+
+
 @pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
 @pytest.mark.parametrize("ext", [(2, 37, 19), (3, 18, 40), (4, 50, 9), (5, 33, 21), (7, 16, 30), (33, 65, 5)], ids=str)
 def test_tile_groups_across_runs(ext, dtype):
