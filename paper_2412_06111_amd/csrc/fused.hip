@@ -756,7 +756,8 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_kernel(SttnnArgs a) {
 //
 // A tile with results outside the range where the split is exact (SplitRange) is marked, and
 // sttnn_t4_kernel, launched behind this kernel, forms it again; with no mark that launch
-// takes 4 us.
+// takes 4 us.  A tensor scaled so that its sketches lie below 2^-80, or whose values decay so
+// far inside every tile, pays for both kernels on every tile.
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
@@ -801,11 +802,22 @@ struct X3Layout {
 };
 
 // Whether results leave the range of the split: infinite or NaN (an infinity, or an FP32
-// value above the largest BF16 one, splits into NaN), or so small that a part of the split
-// may have fallen below the smallest BF16 number.
+// value above the largest BF16 one, splits into NaN), so small that a part of the split may
+// have fallen below the smallest BF16 number, or all zero where a value that is not zero
+// entered their sums (every part of every product fell below it; where only some have, a
+// neighbouring result is not zero and too small).  One zero says nothing: sums of ordinary
+// values cancel to it, too, a few among the 100M of a Z_1.
 struct SplitRange {
   uint32_t least = 0xFFFFFFFFu;             // twice the bits of the smallest magnitude, less one: zero is greatest
+  uint32_t lost = 0;                        // whether the sums of values not all zero came out zero
   float nan = 0.f;                          // NaN from the first infinity or NaN on
+  // any: the bits of the values that entered the sums x
+  __device__ __forceinline__ void zeros(const f32x4_t& x, uint32_t any) {
+    uint32_t b = 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) b |= __float_as_uint(x[v]);
+    lost |= b << 1 == 0 && any << 1 != 0 ? 1u : 0u;
+  }
   __device__ __forceinline__ void add(const f32x4_t& x) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -815,7 +827,7 @@ struct SplitRange {
   }
   __device__ __forceinline__ bool left() const {
     constexpr uint32_t kLeast = uint32_t(127 - 80) << 24;      // 2^-80, twice its bits
-    return __any(nan != nan || least < kLeast);
+    return __any(nan != nan || least < kLeast || lost);
   }
 };
 
@@ -890,8 +902,15 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
       b[0] = *reinterpret_cast<const f32x4_t*>(&Ms[ZN::off(iBl, 32 * t + 8 * lg)]);
       b[1] = *reinterpret_cast<const f32x4_t*>(&Ms[ZN::off(iBl, 32 * t + 8 * lg + 4)]);
     };
-    auto split8 = [&](const f32x4_t (&b)[2]) {
+    // any: bits of the column's values (the lane's quarter of them).  R_B^T leaves the look at
+    // zeros to the waves of Z_A, whose sums are of the same values.
+    uint32_t any = 0;
+    auto split8 = [&](const f32x4_t (&b)[2], bool look) {
       const float x[8] = {b[0][0], b[0][1], b[0][2], b[0][3], b[1][0], b[1][1], b[1][2], b[1][3]};
+      if (look) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) any |= __float_as_uint(x[e]);
+      }
       return split3(x);
     };
     if (zA_role) {
@@ -938,11 +957,13 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
             lds_wait_all();
             if (t + 1 < NK) load(t + 1, (t + 1) & 1);
             __builtin_amdgcn_sched_barrier(0);
-            mfma3(y[t & 1], split8(b[t & 1]), zA);
+            mfma3(y[t & 1], split8(b[t & 1], true), zA);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
         // the tile's row range of Z_A for these columns
+        range.zeros(zA[0], any);
+        any = 0;
 #pragma unroll
         for (int rb = 0; rb < KB; ++rb) {
           range.add(zA[rb]);
@@ -990,10 +1011,12 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
           lds_wait_all();
           if (!TT && t + 1 < NK) slab8(Ms, t + 1, b[TT ? 0 : (t + 1) & 1]);
           __builtin_amdgcn_sched_barrier(0);
-          mfma3(y[TT ? i2l : 0][t], split8(b[TT ? 0 : t & 1]), zB);
+          mfma3(y[TT ? i2l : 0][t], split8(b[TT ? 0 : t & 1], !TT), zB);
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (!TT) {                // Z1 rows [i_2][i_B][j1], 64-byte pieces a lane group
+          range.zeros(zB[0], any);
+          any = 0;
 #pragma unroll
           for (int rb = 0; rb < NB; ++rb) {
             range.add(zB[rb]);
@@ -1018,6 +1041,7 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
 
   // (a) R_A and (c) R_1: A = slab (rows i1, K = the sub-tile's 32 columns)
   f32x4_t rA[2][B2][CBR], r1[2][CBR];       // [i1 block][slab][column block]
+  uint32_t any[2][B2] = {};                 // bits of the values of row i1base + 16 h + l16 (the lane's quarter)
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1067,7 +1091,10 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[h][e] = sign * Ms[ZN::off(8 * lg + e, i1base + 16 * h + l16)];
+        for (int e = 0; e < 8; ++e) {
+          v[h][e] = sign * Ms[ZN::off(8 * lg + e, i1base + 16 * h + l16)];
+          any[h][i2l] |= __float_as_uint(v[h][e]);
+        }
       Bf3 x1s[CBR];
 #pragma unroll
       for (int c = 0; c < CBR; ++c) {
@@ -1101,6 +1128,17 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
       range.add(r1[h][c]);
 #pragma unroll
       for (int i = 0; i < B2; ++i) range.add(rA[h][i][c]);
+    }
+  // the lane's results are of rows 4 lg + v: their values are in four other lanes
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < B2; ++i) {
+      const uint64_t b = __ballot(any[h][i] << 1 != 0);
+      const uint32_t rows = static_cast<uint32_t>(b | b >> 16 | b >> 32 | b >> 48);
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        range.zeros(f32x4_t{rA[h][i][0][v], rA[h][i][1][v], 0.f, 0.f}, rows >> (4 * lg + v) & 1 ? 2u : 0u);
     }
   mark();
 #pragma unroll

@@ -73,3 +73,53 @@ def test_values_at_the_ends_of_the_range(P, variant, dims, value):
         assert np.array_equal(g[~hit], want[~hit]), n
         # one product and its sum with zeros, 2^-24 each side
         np.testing.assert_allclose(g[hit], want[hit], rtol=2.0 ** -22, atol=0, err_msg=str(n))
+
+
+ALL = [(1, 2), (1,), (2,), (3, 4), (3,), (4,)]
+
+
+def small(x, e):
+    """x 2^e as FP32 holds it, and the same values times 2^-e (exact both ways)."""
+    s = np.ldexp(np.asarray(x, dtype=np.float64), e).astype(np.float32)
+    return s, np.ldexp(s.astype(np.float64), -e).astype(np.float32)
+
+
+def small_tol(K, e):
+    """FP32 arithmetic of two runs, and sums of K products of size 2^e that FP32 holds in
+    steps of 2^-149: K roundings of up to half a step in a sum of about sqrt(K) 2^e."""
+    return 2.0 ** -20 + np.sqrt(K) * 2.0 ** (-150 - e)
+
+
+@pytest.mark.parametrize("variant", ["sttnn", "ttnn"])
+@pytest.mark.parametrize("dims", SHAPES, ids=str)
+@pytest.mark.parametrize("e", [-120, -133, -140])
+def test_small_tensors(P, variant, dims, e):
+    """Tensors whose split parts fall below the smallest BF16 number: the second part
+    (2^-120), nearly all of the first (2^-133) and every part (2^-140, FP32 subnormals)."""
+    T, up = small(np.random.default_rng(4).standard_normal(dims), e)
+    plan = P.Plan(O.T4, dims, R, P_, variant=variant, dtype="f32", seed=6)
+    one, got = sketches(P, plan, up, ALL), sketches(P, plan, T, ALL)
+    tol = small_tol(max(np.prod(dims[:2]), np.prod(dims[2:])), e)
+    bad = {n: v for n, a, b in zip(ALL, one, got) if not (v := errs2(np.ldexp(b, -e), a)[0]) <= tol}
+    assert not bad, (bad, tol)
+
+
+@pytest.mark.parametrize("variant", ["sttnn", "ttnn"])
+@pytest.mark.parametrize("dims", SHAPES, ids=str)
+@pytest.mark.parametrize("e", [-120, -140])
+def test_small_rows_and_columns(P, variant, dims, e):
+    """One row (i_1, i_2) and one column (i_3, i_4) of small values in a tensor of ordinary
+    ones: their rows of the sketches of (1, 2) and (3, 4) are those of the values scaled up."""
+    g = np.random.default_rng(5)
+    T = g.standard_normal(dims).astype(np.float32)
+    big = T.copy()
+    T[77, 5], big[77, 5] = small(T[77, 5], e)
+    col, up = small(T[:, :, 9, 13], e)
+    T[:, :, 9, 13], big[:, :, 9, 13] = col, up
+    T[77, 5, 9, 13] = big[77, 5, 9, 13] = 0.0
+    plan = P.Plan(O.T4, dims, R, P_, variant=variant, dtype="f32", seed=6)
+    row, cl = 77 + 128 * 5, 9 + dims[2] * 13
+    for node, at, K in (((1, 2), row, np.prod(dims[2:])), ((3, 4), cl, np.prod(dims[:2]))):
+        (a,), (b,) = (sketches(P, plan, x, [node]) for x in (big, T))
+        err = np.linalg.norm(np.ldexp(b[at], -e) - a[at]) / np.linalg.norm(a[at])
+        assert err <= small_tol(K, e), (node, err, small_tol(K, e))
