@@ -749,10 +749,11 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_kernel(SttnnArgs a) {
 // copy of X_1 would add 134 MB to the sweep's bytes).  That leaves room for four stages of T:
 // waves 0, 1, which load nothing else, issue the slab's copies three sub-tiles ahead.
 //
-// 128^4, r = 32, whole update, in turns with the FP32 MFMA form: STTNN 1028 -> 807 us, TTNN
-// 1648 -> 1432 us (with two stages, Y_1 in LDS and the copies issued by all waves 1003 and
-// 1512).  The sketches' errors against FP64 are below those of the FP32 MFMA form (R_1 of a
-// 128^4 tensor 3e-7, there 1.6e-6).
+// 128^4, r = 32, whole update, in turns with the FP32 MFMA form: STTNN 1021 -> 814 us, TTNN
+// 1660 -> 1459 us (with two stages, Y_1 in LDS and the copies issued by all waves a quarter
+// more for STTNN).  Over twelve shapes and five kinds of data the sketches' errors against
+// FP64 are 0.2 to 0.75 of those of the FP32 MFMA form (R_1 of a 128^4 tensor 3e-7, there
+// 1.6e-6), R_2's, whose second pass is the same in both, 0.8 to 1.07.
 //
 // A tile with results outside the range where the split is exact (SplitRange) is marked, and
 // sttnn_t4_kernel, launched behind this kernel, forms it again; with no mark that launch
@@ -895,6 +896,10 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
     // i1, columns).  Waves 0, 1 take Z_A, its A rows from LDS; waves 2, 3 the other, whose A
     // fragments (the same for every sub-tile of a slab) stay in registers, which leaves the
     // LDS to two more stages of T.
+    // The BF16 MFMA rounds its sums down, which adds up over the tiles: every second step's
+    // products go, negated (the planes hold those values of Y_A, Y_1 and X_B so), to sums of
+    // their own, where down is the other way.  R_B of a 128 x 1024 x 8 x 4 tensor is 1.6e-7 off
+    // its FP64 value (4.2e-7 in one chain, 2.8e-7 on the FP32 MFMA).
     const int iBl = 16 * (wave % NCB) + l16;
     const bool zA_role = wave < NCB;
     constexpr int NB = TT ? CBR : KB, NS = TT ? B2 : 1;      // row blocks, slabs with rows of their own
@@ -914,7 +919,7 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
       return split3(x);
     };
     if (zA_role) {
-      f32x4_t zA[KB];
+      f32x4_t zA[2][KB];
       float* PZ = static_cast<float*>(a.PZA) + static_cast<int64_t>(tA) * KP * nB + c_tile + iBl;
 #pragma unroll
       for (int s = 0; s < NST - 1; ++s) issue(s);
@@ -933,7 +938,7 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
       static_assert(KB == 3 && NST == 4 && B2 == 2, "the counts of copy_stage");
       for (int cb = 0; cb < a.CB; ++cb) {
 #pragma unroll
-        for (int rb = 0; rb < KB; ++rb) zA[rb] = zero;
+        for (int rb = 0; rb < KB; ++rb) zA[0][rb] = zA[1][rb] = zero;
 #pragma unroll
         for (int i2l = 0; i2l < B2; ++i2l) {
           copy_stage(cb * B2 + i2l);
@@ -957,19 +962,20 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
             lds_wait_all();
             if (t + 1 < NK) load(t + 1, (t + 1) & 1);
             __builtin_amdgcn_sched_barrier(0);
-            mfma3(y[t & 1], split8(b[t & 1], true), zA);
+            mfma3(y[t & 1], split8(b[t & 1], true), zA[t & 1]);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
         // the tile's row range of Z_A for these columns
-        range.zeros(zA[0], any);
-        any = 0;
 #pragma unroll
         for (int rb = 0; rb < KB; ++rb) {
-          range.add(zA[rb]);
+          const f32x4_t z = zA[0][rb] - zA[1][rb];
+          if (rb == 0) range.zeros(z, any);
+          range.add(z);
 #pragma unroll
-          for (int v = 0; v < 4; ++v) PZ[(16 * rb + 4 * lg + v) * nB + cb * SC] = zA[rb][v];
+          for (int v = 0; v < 4; ++v) PZ[(16 * rb + 4 * lg + v) * nB + cb * SC] = z[v];
         }
+        any = 0;
       }
       __builtin_amdgcn_s_waitcnt(0);        // no copy outlives the workgroup
       mark();
@@ -991,7 +997,7 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
                   bf16x8_t, *reinterpret_cast<const u16x8_t*>(Y + (p * rows + 16 * rb + l16) * ld +
                                                               (TT ? (i2_0 + i) * N1 : 0) + 32 * t + 8 * lg));
     }
-    f32x4_t zB[NB];
+    f32x4_t zB[2][NB];
     float* PZ = TT ? static_cast<float*>(a.PRB) + static_cast<int64_t>(tA) * R * nB + c_tile + iBl
                    : static_cast<float*>(a.Z1) + (i2_0 * nB + c_tile + iBl) * KP + 4 * lg;
     for (int cb = 0; cb < a.CB; ++cb) {
@@ -999,7 +1005,7 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
       for (int i2l = 0; i2l < B2; ++i2l) {
         if (!TT || i2l == 0) {
 #pragma unroll
-          for (int rb = 0; rb < NB; ++rb) zB[rb] = zero;
+          for (int rb = 0; rb < NB; ++rb) zB[0][rb] = zB[1][rb] = zero;
         }
         next_stage();
         const float* Ms = stage(cb * B2 + i2l);
@@ -1011,27 +1017,29 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
           lds_wait_all();
           if (!TT && t + 1 < NK) slab8(Ms, t + 1, b[TT ? 0 : (t + 1) & 1]);
           __builtin_amdgcn_sched_barrier(0);
-          mfma3(y[TT ? i2l : 0][t], split8(b[TT ? 0 : t & 1], !TT), zB);
+          mfma3(y[TT ? i2l : 0][t], split8(b[TT ? 0 : t & 1], !TT), zB[t & 1]);
           __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (!TT) {                // Z1 rows [i_2][i_B][j1], 64-byte pieces a lane group
-          range.zeros(zB[0], any);
-          any = 0;
 #pragma unroll
           for (int rb = 0; rb < NB; ++rb) {
-            range.add(zB[rb]);
-            *reinterpret_cast<f32x4_t*>(PZ + (i2l * nB + cb * SC) * KP + 16 * rb) = zB[rb];
+            const f32x4_t z = zB[0][rb] - zB[1][rb];
+            if (rb == 0) range.zeros(z, any);
+            range.add(z);
+            *reinterpret_cast<f32x4_t*>(PZ + (i2l * nB + cb * SC) * KP + 16 * rb) = z;
           }
+          any = 0;
         }
       }
       if constexpr (TT) {                   // the tile's row range of R_B^T for these columns
 #pragma unroll
         for (int rb = 0; rb < NB; ++rb) {
-          range.add(zB[rb]);
+          const f32x4_t z = zB[0][rb] - zB[1][rb];
+          range.add(z);
           int64_t ld = nB;                  // the rows' addresses formed here, not held through the loop
           asm volatile("" : "+s"(ld));
 #pragma unroll
-          for (int v = 0; v < 4; ++v) PZ[(16 * rb + 4 * lg + v) * ld + cb * SC] = zB[rb][v];
+          for (int v = 0; v < 4; ++v) PZ[(16 * rb + 4 * lg + v) * ld + cb * SC] = z[v];
         }
       }
     }
@@ -1741,7 +1749,8 @@ __global__ void gather_copy(const double* src, TO* out, int64_t d0, int64_t d1, 
   }
 }
 
-// The same copy split into the BF16 planes of split3: out[p][o], p = h, m, l.
+// The same copy split into the BF16 planes of split3: out[p][o], p = h, m, l, every second
+// 32 values of i_0 negated (sttnn_t4_x3_kernel's second sums).
 __global__ void gather_split(const double* src, uint16_t* out, int64_t d0, int64_t d1, int64_t s0, int64_t s1,
                              int64_t lim) {
   const int64_t total = d0 * d1;
@@ -1749,6 +1758,7 @@ __global__ void gather_split(const double* src, uint16_t* out, int64_t d0, int64
        o += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     const int64_t i0 = o % d0, i1 = o / d0;
     float v = i1 < lim ? static_cast<float>(src[i0 * s0 + i1 * s1]) : 0.0f;
+    if (i0 & 32) v = -v;
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       const uint32_t b = __float_as_uint(v);

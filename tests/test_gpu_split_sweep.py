@@ -123,3 +123,36 @@ def test_small_rows_and_columns(P, variant, dims, e):
         (a,), (b,) = (sketches(P, plan, x, [node]) for x in (big, T))
         err = np.linalg.norm(np.ldexp(b[at], -e) - a[at]) / np.linalg.norm(a[at])
         assert err <= small_tol(K, e), (node, err, small_tol(K, e))
+
+
+@pytest.mark.parametrize("variant", ["sttnn", "ttnn"])
+def test_rounding_has_no_direction(P, variant):
+    """The sums of Y_A, Y_1 and X_B rows with the tensor (Z_A, Z_1 and R_B) are off to either
+    side alike: their mean error is within five standard deviations of the mean of as many
+    independent errors.  Sums that are all rounded one way add up over the 512 tiles of this
+    tensor: R_B was 20 such deviations off.  Z_A is the root's sketch undone (its 32 columns times a
+    32 x 48 map), Z_1's mean error a projection of R_2's errors on the columns' sums of X_2."""
+    dims = (128, 1024, 32)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    T = torch.randn(int(np.prod(dims)), generator=g, device="cuda", dtype=torch.float32)
+    M = T.double().view(32, 128 * 1024).t()
+    plan = P.Plan(((1, 2), 3), dims, R, P_, variant=variant, dtype="f32", seed=6)
+    plan.update(T)
+    A, B, one, two = (plan.node(m) for m in ((1, 2), (3,), (1,), (2,)))
+    X = {v: plan.read_drm(v, 0) for v in (B, two)}
+    Y = {v: plan.read_drm(v, 1) for v in (A, B, one)}
+    k = R + P_
+    ZA = Y[A].t() @ M
+    off = {"Z_A": plan.read_sketch(0, P.SK_PSI).view(k, k).t() @ torch.linalg.pinv(Y[B]) - ZA}
+    if variant == "ttnn":
+        off["R_B"] = plan.read_sketch(B, P.SK_R) - M.t() @ X[B]
+    else:
+        Z1 = torch.einsum("cba,aj->bcj", M.t().reshape(32, 1024, 128), Y[one]).reshape(1024, -1)   # [i_2][(i_3, j)]
+        X2 = X[two].view(32, k, R).reshape(32 * k, R)                                              # rows j + k i_3
+        w = X2.sum(0)
+        off["Z_1"] = (plan.read_sketch(two, P.SK_R) - Z1 @ X2) @ w / (w @ w)
+    for name, d in off.items():
+        sd = float(d.std()) / np.sqrt(d.numel())
+        print(name, float(d.mean()) / sd, flush=True)
+        assert abs(float(d.mean())) <= 5 * sd, (name, float(d.mean()), sd)
+    plan.close()
