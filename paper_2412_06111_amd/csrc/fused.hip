@@ -1400,7 +1400,9 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_f64_kernel(SttnnArgs a) {
 // those of sttnn_t4_f64_kernel: waves 0, 1 Z_A and the copies of T and X_1, three sub-tiles
 // ahead into four stages, and of X_A, a column block ahead; waves 2, 3 Z1, Y_1 in registers,
 // written straight from the products; waves 4-7 R_A and R_1.  The Y_A rows of the four slabs
-// (96 KB) stay in LDS.
+// (96 KB) stay in LDS.  Z_A's FP32 sums start anew for every slab and are then added: in one
+// chain over the four slabs Z_A was 1.4 times as far from its FP64 value as with two slabs a
+// tile, now 0.85 times.
 // 128^4, r = 64: the sweep 540 -> 440 us and the reduction of its partials 103 -> 63, the
 // whole update 1083 -> 944 (sttnn_t4_kernel: two slabs, Z1 through an LDS stash, every wave
 // waiting for its copies; with the X values fetched by waves 4-7 a sub-tile ahead: 583).
@@ -1512,6 +1514,9 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_bf64_kernel(SttnnArgs a) {
           __builtin_amdgcn_sched_barrier(0);
           const uint16_t* Ms = stage(cb * B2 + i2l);
           const uint16_t* Ys = YRs + i2l * KP * N1;
+          f32x4_t z[KB];                    // this slab's sums (see above)
+#pragma unroll
+          for (int rb = 0; rb < KB; ++rb) z[rb] = zero;
           bf16x8_t b[2], y[2][KB];
           auto load = [&](int t, int q) {
             b[q] = frag(Ms, iBl, 32 * t + 8 * lg);
@@ -1525,9 +1530,11 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_bf64_kernel(SttnnArgs a) {
             if (t + 1 < NK) load(t + 1, (t + 1) & 1);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int rb = 0; rb < KB; ++rb) zA[rb] = P::mfma(y[t & 1][rb], b[t & 1], zA[rb]);
+            for (int rb = 0; rb < KB; ++rb) z[rb] = P::mfma(y[t & 1][rb], b[t & 1], z[rb]);
             __builtin_amdgcn_sched_barrier(0);
           }
+#pragma unroll
+          for (int rb = 0; rb < KB; ++rb) zA[rb] += z[rb];
         }
 #pragma unroll
         for (int rb = 0; rb < KB; ++rb)     // the tile's row range of Z_A for these columns
@@ -1881,10 +1888,8 @@ void fused_prepare(Plan& P, hipStream_t st) {
   const int zdt = P.dtype == TTNN_BF16 ? TTNN_F32 : P.dtype;
   const bool zout = !tt && R >= 32 && right_mfma_eligible(static_cast<int64_t>(KP) * nB, n2, 1, R, zdt);
   Shape sh = shape_for(P.dtype, R, tt, zout);
-  // sttnn_t4_bf64_kernel where four slabs a tile divide n_2 (the two-slab form where two do)
-  if (P.dtype == TTNN_BF16 && R == 64 && zout && n2 % Bf64Layout::B2 == 0) sh.B2 = Bf64Layout::B2;
   if (n2 % sh.B2 != 0 || nB % sh.SC != 0) return;
-  const int TA = static_cast<int>(n2 / sh.B2);
+  int TA = static_cast<int>(n2 / sh.B2);
   // column tiles: the fewest that give every compute unit a tile (else as many as divide)
   int TB = 0;
   for (int cand = 1; cand <= 256; cand *= 2) {
@@ -1893,6 +1898,14 @@ void fused_prepare(Plan& P, hipStream_t st) {
     if (static_cast<int64_t>(TA) * cand >= 256) break;
   }
   if (TB == 0) return;
+  // sttnn_t4_bf64_kernel, tiles of twice the slabs by half the columns, where both divide: R_1's
+  // sums run over as many products as in the two-slab form's tiles
+  if (P.dtype == TTNN_BF16 && R == 64 && zout && n2 % Bf64Layout::B2 == 0 && TB <= 128 &&
+      nB % (static_cast<int64_t>(sh.SC) * 2 * TB) == 0) {
+    sh.B2 = Bf64Layout::B2;
+    TA /= 2;
+    TB *= 2;
+  }
   F.R = R;
   F.KP = KP;
   F.k = nA_.k;

@@ -42,3 +42,24 @@ def test_bf16_sweep_edges(dims, p):
     sk = O.sketch(consumed, tree, O.DRMs(tree, 9, "sttnn", "bf16"), "sttnn")
     bad = failures(sketch_errors(plan, tree, sk), TOL_ARITH["bf16"])
     assert not bad, bad
+
+
+@pytest.mark.parametrize("dims,p", [((128, 132, 8, 32), 1), ((128, 512, 8, 24), 32), ((128, 68, 16, 64), 32), ((128, 1024, 8, 4), 32)], ids=str)
+def test_bf16_sums_of_two_slabs(dims, p):
+    """Sketches that follow from Z_A at BF16, r = 64, four slabs a tile (one column block a
+    tile, three, two) and two (1,024 of one column block), over several tiles a sketch.  A
+    product adds with an error of one FP32 rounding (2.5e-8 of the sum, rms) or two; sums of
+    the eight products of two slabs, the former tiles, come out sqrt(9 / 2) to sqrt(9) times
+    that, 5.3e-8 to 7.5e-8.  Sixteen products in one chain are at 1.3e-7."""
+    import paper_2412_06111_amd as P
+    T = np.random.default_rng(23).standard_normal(dims)
+    dev, consumed = to_device(T, "bf16")
+    plan = P.Plan(O.T4, dims, 64, p, variant="sttnn", dtype="bf16", seed=9)
+    plan.update(dev)
+    tree = O.Tree(O.T4, dims, 64, p)
+    sk = O.sketch(consumed, tree, O.DRMs(tree, 9, "sttnn", "bf16"), "sttnn")
+    errs = sketch_errors(plan, tree, sk)
+    got = {k: errs[k][0] for k in (("psi", (1, 2, 3, 4)), ("R", (3, 4)), ("R", (3,)), ("R", (4,)))}
+    print(got, flush=True)
+    assert max(got.values()) <= 1e-7, got
+    assert errs["R", (1, 2)][0] <= 1.5e-7 and errs["R", (1,)][0] <= 2e-7, errs
