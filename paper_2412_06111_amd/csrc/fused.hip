@@ -1679,9 +1679,30 @@ __device__ inline void reduce_transpose_tile(const Acc* P, int nt, int64_t tstri
   }
 }
 
+// Few entries, many partials: O[x + ldo y] = sum_t P[t * tstride + x * ldx + y] for 32 values
+// of y at one x, eight threads an entry (thread g sums t = g mod 8), their sums added in a
+// fixed tree.
+constexpr int kSplitY = 32, kSplitT = 256 / kSplitY;
+template <typename Acc>
+__device__ inline void reduce_split_row(const Acc* P, int nt, int64_t tstride, int64_t ldx, int64_t Y, int64_t x,
+                                        int64_t y0, double* O, int64_t ldo, double* red) {
+  const int yl = threadIdx.x % kSplitY, g = threadIdx.x / kSplitY;
+  const int64_t y = y0 + yl;
+  double v = 0.0;
+  if (y < Y && g < nt) v = sum_strided(P + g * tstride + x * ldx + y, (nt - g + kSplitT - 1) / kSplitT, kSplitT * tstride);
+  red[g * kSplitY + yl] = v;
+  __syncthreads();
+#pragma unroll
+  for (int w = kSplitT / 2; w > 0; w /= 2) {
+    if (g < w) red[g * kSplitY + yl] += red[(g + w) * kSplitY + yl];
+    __syncthreads();
+  }
+  if (g == 0 && y < Y) O[x + ldo * y] = red[yl];
+}
+
 // Sum the tile partials in a fixed order into the FP64 state.  Blocks [0, nbA) do R_A
 // (PRA [tB][iA][R] -> RA[iA + nA j]) and [nbA, nbA + nbZ) Z_A (PZA [tA][jA][iB] ->
-// ZA[jA + k iB]) tile by tile, [nbA + nbZ, + nb1) R_1 (16 lanes per entry), and the
+// ZA[jA + k iB]) tile by tile (zsplit: 32 entries a block), [nbA + nbZ, + nb1) R_1 (16 lanes per entry), and the
 // remaining blocks the last segment, entry by entry: R_2 (mode 0, STTNN; PR2
 // [tB][n2][R]), R_B (mode 1, TTNN; PRB [tA][R][nB]) or nothing (mode 2, STTNN with Z1
 // written out).
@@ -1689,7 +1710,7 @@ template <typename Acc>
 __global__ __launch_bounds__(256) void sttnn_t4_reduce(const Acc* PRA, const Acc* PZA, const Acc* PR1, const Acc* PR2,
                                                        int TA, int TB, int64_t n2, int64_t nA, int64_t nB, int R,
                                                        int KP, int k, double alpha, double* RA, double* ZA, double* R1,
-                                                       double* R2, int tt, int nbA, int nbZ, int nb1) {
+                                                       double* R2, int tt, int nbA, int nbZ, int zsplit, int nb1) {
   __shared__ double tile[kRTY][kRTX + 1];
   const int64_t b = blockIdx.x;
   if (b < nbA) {
@@ -1699,6 +1720,10 @@ __global__ __launch_bounds__(256) void sttnn_t4_reduce(const Acc* PRA, const Acc
   }
   if (b < nbA + nbZ) {
     const int64_t bz = b - nbA;
+    if (zsplit) {
+      reduce_split_row(PZA, TA, static_cast<int64_t>(KP) * nB, nB, nB, bz % k, (bz / k) * kSplitY, ZA, k, &tile[0][0]);
+      return;
+    }
     const int64_t tx = (k + kRTX - 1) / kRTX;
     reduce_transpose_tile(PZA, TA, static_cast<int64_t>(KP) * nB, nB, k, nB, (bz % tx) * kRTX, (bz / tx) * kRTY, ZA,
                           k, 1.0, false, tile);
@@ -2035,7 +2060,14 @@ bool try_fused_update(Plan& P, const void* block, const int64_t* off, const int6
   const int node_last = F.tt ? F.node_B : F.node_2;
   const void* plast = F.tt ? F.PRB : F.PR2;
   const int64_t nbA = ((F.nA + kRTX - 1) / kRTX) * ((F.R + kRTY - 1) / kRTY);
-  const int64_t nbZ = ((F.k + kRTX - 1) / kRTX) * ((F.nB + kRTY - 1) / kRTY);
+  // Z_A: a tile's threads sum an entry's TA partials by themselves, which leaves the chip idle
+  // where there are fewer tiles than compute units; then eight threads share an entry.  r = 32,
+  // whole update, one thread and eight: 128 x 1024 x 32 FP64 (512 partials, 3 tiles) 210 -> 170
+  // us, 128 x 1024 x 1024 FP32 (96 tiles) 538 -> 492, 128 x 256 x 1024 FP64 327 -> 312, 128 x 32 x
+  // 4096 (16 partials, 384 tiles) as before.
+  const int64_t zt = ((F.k + kRTX - 1) / kRTX) * ((F.nB + kRTY - 1) / kRTY);
+  const bool zsplit = zt < 256 && F.TA >= 2 * kSplitT;
+  const int64_t nbZ = zsplit ? F.k * ((F.nB + kSplitY - 1) / kSplitY) : zt;
   const int mode = F.tt ? 1 : F.zout ? 2 : 0;
   const int64_t nb1 = (static_cast<int64_t>(N1) * F.R * 16 + 255) / 256;
   const int64_t rest = (F.tt ? F.nB : F.zout ? 0 : F.n2) * F.R;
@@ -2046,13 +2078,13 @@ bool try_fused_update(Plan& P, const void* block, const int64_t* off, const int6
                        static_cast<const double*>(F.PZA), static_cast<const double*>(F.PR1),
                        static_cast<const double*>(plast), F.TA, F.TB, F.n2, F.nA, F.nB, F.R, F.KP, F.k, alpha,
                        P.nodes[F.node_A].R, ZA, P.nodes[F.node_1].R, P.nodes[node_last].R, mode,
-                       static_cast<int>(nbA), static_cast<int>(nbZ), static_cast<int>(nb1));
+                       static_cast<int>(nbA), static_cast<int>(nbZ), zsplit ? 1 : 0, static_cast<int>(nb1));
   else
     hipLaunchKernelGGL(sttnn_t4_reduce<float>, grid, dim3(256), 0, st, static_cast<const float*>(F.PRA),
                        static_cast<const float*>(F.PZA), static_cast<const float*>(F.PR1),
                        static_cast<const float*>(plast), F.TA, F.TB, F.n2, F.nA, F.nB, F.R, F.KP, F.k, alpha,
                        P.nodes[F.node_A].R, ZA, P.nodes[F.node_1].R, P.nodes[node_last].R, mode,
-                       static_cast<int>(nbA), static_cast<int>(nbZ), static_cast<int>(nb1));
+                       static_cast<int>(nbA), static_cast<int>(nbZ), zsplit ? 1 : 0, static_cast<int>(nb1));
   done_nodes->assign({F.node_A, F.node_1, node_last});
   done_prefixes->assign({pre});
   return true;

@@ -63,3 +63,19 @@ def test_bf16_sums_of_two_slabs(dims, p):
     print(got, flush=True)
     assert max(got.values()) <= 1e-7, got
     assert errs["R", (1, 2)][0] <= 1.5e-7 and errs["R", (1,)][0] <= 2e-7, errs
+
+
+@pytest.mark.parametrize("variant,dtype", [("sttnn", "f64"), ("sttnn", "f32"), ("ttnn", "f32")])
+@pytest.mark.parametrize("dims", [(128, 30, 8, 12), (128, 32, 4, 8), (128, 46, 8, 12), (128, 32, 48, 56), (128, 32, 64, 44)], ids=str)
+def test_sums_of_many_tiles(dims, variant, dtype):
+    """Z_A's partials summed by one thread an entry and by eight: 15, 16 and 23 tiles of two
+    slabs; 252 and 264 tiles of entries for 256 compute units."""
+    import paper_2412_06111_amd as P
+    T = np.random.default_rng(24).standard_normal(dims)
+    dev, consumed = to_device(T, dtype)
+    plan = P.Plan(O.T4, dims, 32, 16, variant=variant, dtype=dtype, seed=9)
+    plan.update(dev)
+    tree = O.Tree(O.T4, dims, 32, 16)
+    sk = O.sketch(consumed, tree, O.DRMs(tree, 9, variant, dtype), variant)
+    bad = failures(sketch_errors(plan, tree, sk), TOL_ARITH[dtype])
+    assert not bad, bad
