@@ -148,15 +148,14 @@ struct Swz {
 // Copy `rows` rows of RL elements (row r from g + r*gs) into LDS at l, swizzled:
 // each instruction fills 64 / CPR whole rows (64 lanes x 16 bytes, one contiguous
 // kilobyte of LDS); lane L fetches the chunk that belongs at its position.
-// Instructions are dealt to NW waves, of which this is number `wave`; the LDS address is
-// wave-uniform.
-template <typename T, int RL, int NW = kThreadsF / 64>
+// Instructions are dealt to the eight waves; the LDS address is wave-uniform.
+template <typename T, int RL>
 __device__ inline void lds_dma_rows(const T* g, int64_t gs, T* l, int rows, int wave, int lane) {
   using Z = Swz<T, RL>;
   constexpr int RPI = 64 / Z::CPR;                    // rows per instruction
   const int ninstr = rows / RPI;
   const int rl = lane / Z::CPR, p = lane % Z::CPR;
-  for (int q = wave; q < ninstr; q += NW) {
+  for (int q = wave; q < ninstr; q += kThreadsF / 64) {
     const int r = q * RPI + rl;
     const int c = p ^ (r & Z::MASK);
     lds_dma16(g + r * gs + static_cast<int64_t>(c) * Z::EV, l + q * RPI * RL);

@@ -96,37 +96,16 @@ __global__ void fold_chunks_kernel(double* __restrict__ part, int nchunks, int64
   part[c0 * E + e] = sum_chunks(part, c0, c1, E, e);
 }
 
-__global__ void zero_kernel(double* p, int64_t n) {
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    p[i] = 0.0;
-}
-__global__ void axpy_kernel(double* y, const double* x, double alpha, int64_t n) {
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    y[i] += alpha * x[i];
-}
 __global__ void copy_kernel(double* y, const double* x, int64_t n) {
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)
     y[i] = x[i];
-}
-__global__ void f64_to_f32_kernel(float* y, const double* x, int64_t n) {
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    y[i] = static_cast<float>(x[i]);
 }
 __global__ void zero_int_kernel(int* p, int64_t n) {
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * blockDim.x)
     p[i] = 0;
 }
-__global__ void finite_kernel(const double* p, int64_t n, int* flag) {
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    if (!isfinite(p[i])) *flag = 1;
-}
-
 // Block b of a list launch serves segment `seg` (blocks are dealt to segments in
 // proportion to their length, at most kSegBlocks each).
 __device__ inline int seg_of(const SegList& s, int b, int* first) {
@@ -278,16 +257,6 @@ void launch_gemm_staged(const BatchedGemm& b, const GemmTask* d, hipStream_t st)
   kernels_for(b.th, b.td).table(d, nt, GemmTask{}, b.blocks, b.lds, st);
 }
 
-void launch_gemm_batched(const std::vector<GemmArgs>& args, hipStream_t st) {
-  const BatchedGemm b = plan_gemm_batched(args);
-  if (b.tasks.empty()) return;
-  StagingLock lock;
-  const GemmTask* d =
-      static_cast<const GemmTask*>(stage_descriptors(b.tasks.data(), b.tasks.size() * sizeof(GemmTask), st));
-  launch_gemm_staged(b, d, st);
-  fence_descriptors(st);
-}
-
 void launch_level_lin(const std::vector<GemmArgs>& args, const std::vector<ReduceTask>& reds, hipStream_t st) {
   std::vector<bool> taken(args.size(), false);
   for (size_t a = 0; a < args.size(); ++a) {              // one launch per operand type
@@ -305,15 +274,17 @@ void launch_level_lin(const std::vector<GemmArgs>& args, const std::vector<Reduc
       if (taken[b] || args[b].th != args[a].th || args[b].td != args[a].td) continue;
       taken[b] = true;
       GemmTask t{};
-      if (!fill_task(args[b], t, lds)) continue;
+      size_t mem = 0;
+      if (!fill_task(args[b], t, mem)) continue;
       const int64_t mine = t.row_blocks * t.nch * t.col_blocks;
-      TTNN_REQUIRE(!args[b].hm.strided && t.sDc == 1 && t.row_blocks < (int64_t(1) << 31) && t.nch < (int64_t(1) << 31) &&
-                       blocks + mine < (int64_t(1) << 31), TTNN_E_INVALID, "contraction launch too large");
+      TTNN_REQUIRE(!args[b].hm.strided && t.sDc == 1 && mine < (int64_t(1) << 31), TTNN_E_INVALID,
+                   "contraction launch too large");
+      if (v.size() == static_cast<size_t>(kLinTasks) || blocks + mine >= (int64_t(1) << 31)) flush();
       v.push_back(GemmLin{t.H, t.D, t.out, t.L, t.n, t.Q, t.sDr, t.kchunk, t.ncols, t.tr, t.ncb, t.right,
                           static_cast<int32_t>(blocks), static_cast<int32_t>(t.row_blocks), static_cast<int32_t>(t.nch),
                           t.ol.cs == 0 ? 1 : 0});
       blocks += mine;
-      if (v.size() == static_cast<size_t>(kLinTasks)) flush();
+      lds = std::max(lds, mem);
     }
     flush();
   }
@@ -383,19 +354,6 @@ void launch_reduce_staged(const BatchedReduce& b, const ReduceTask* dfolds, cons
                      static_cast<int>(b.tasks.size()));
 }
 
-void launch_reduce_batched(const std::vector<ReduceTask>& in, hipStream_t st) {
-  const BatchedReduce b = plan_reduce_batched(in);
-  if (b.tasks.empty()) return;
-  StagingLock lock;
-  const ReduceTask* df = nullptr;
-  if (!b.folds.empty())
-    df = static_cast<const ReduceTask*>(stage_descriptors(b.folds.data(), b.folds.size() * sizeof(ReduceTask), st));
-  const ReduceTask* dt =
-      static_cast<const ReduceTask*>(stage_descriptors(b.tasks.data(), b.tasks.size() * sizeof(ReduceTask), st));
-  launch_reduce_staged(b, df, dt, st);
-  fence_descriptors(st);
-}
-
 void launch_reduce(double* part, int nchunks, int64_t rows, int ncols, int mode, double alpha,
                    const IndexMap& rmap, int64_t ldr, double* dst, int64_t L, int64_t kdim, hipStream_t st) {
   if (rows <= 0 || ncols <= 0) return;
@@ -412,17 +370,8 @@ void launch_reduce(double* part, int nchunks, int64_t rows, int ncols, int mode,
                      rmap, ldr, dst, L, kdim, stride);
 }
 
-void launch_zero(double* p, int64_t n, hipStream_t st) {
-  if (n > 0) hipLaunchKernelGGL(zero_kernel, dim3(grid_for(n)), dim3(256), 0, st, p, n);
-}
-void launch_axpy(double* y, const double* x, double alpha, int64_t n, hipStream_t st) {
-  if (n > 0) hipLaunchKernelGGL(axpy_kernel, dim3(grid_for(n)), dim3(256), 0, st, y, x, alpha, n);
-}
 void launch_copy_f64(double* y, const double* x, int64_t n, hipStream_t st) {
   if (n > 0) hipLaunchKernelGGL(copy_kernel, dim3(grid_for(n)), dim3(256), 0, st, y, x, n);
-}
-void launch_f64_to_f32(float* y, const double* x, int64_t n, hipStream_t st) {
-  if (n > 0) hipLaunchKernelGGL(f64_to_f32_kernel, dim3(grid_for(n)), dim3(256), 0, st, y, x, n);
 }
 void launch_zero_int(int* p, int64_t n, hipStream_t st) {
   if (n > 0) hipLaunchKernelGGL(zero_int_kernel, dim3(grid_for(n)), dim3(256), 0, st, p, n);
@@ -440,10 +389,6 @@ void launch_zero_list(const SegList& s, hipStream_t st) {
 }
 void launch_finite_list(const SegList& s, int* flag, hipStream_t st) {
   if (s.count > 0) hipLaunchKernelGGL(finite_list_kernel, dim3(list_blocks(s)), dim3(256), 0, st, s, flag);
-}
-
-void launch_finite_check(const double* p, int64_t n, int* flag, hipStream_t st) {
-  if (n > 0) hipLaunchKernelGGL(finite_kernel, dim3(grid_for(n)), dim3(256), 0, st, p, n, flag);
 }
 
 // ---------------------------------------------------------------- persistent ingest (host)

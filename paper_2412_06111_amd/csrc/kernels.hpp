@@ -19,7 +19,8 @@ void launch_eye(int64_t n, double* o64, float* o32, uint16_t* o16, hipStream_t s
 //   RIGHT: out(c; i, j) = sum_{m in chunk c} Hm(m, i) D(drow(m), j),
 //          drow(m) = amap(m % L) + bmap(m / L)
 //   LEFT : out(c; m, j) = sum_{i in chunk c} Hm(m, i) D(drow(i), j),  drow(i) = amap(i)
-// D(row, j) = D[row * sDr + j * sDc] (dtype td).  Results are FP64, stored at  out[c*cs + (row % Lo)*s0 + j*s1 + (row / Lo)*s2].
+// D(row, j) = D[row * sDr + j * sDc] (dtype td).  Results are FP64, stored at
+// out[c*cs + (row % Lo)*s0 + j*s1 + (row / Lo)*s2].
 struct OutLayout {
   int64_t Lo, s0, s1, s2, cs;
 };
@@ -102,14 +103,11 @@ struct ReduceLin {
   int32_t nchunks, ncols, mode, first_block, nblocks, pad_;
 };
 constexpr int kLinTasks = 24;
-// Launch the generic contractions of one operand type (right and left) for every element of `args` in one kernel: each workgroup serves one tile of one task.
-// Results are bitwise those of launch_gemm on each element.
-void launch_gemm_batched(const std::vector<GemmArgs>& args, hipStream_t stream);
-// Fixed-order partial sums of several contractions in one launch (see launch_reduce).
-void launch_reduce_batched(const std::vector<ReduceTask>& tasks, hipStream_t stream);
-// The same two launches split into building the descriptor tables on the host and
-// launching from tables already staged on the device, so that a caller can stage the
-// tables of many launches in one copy.
+// The contractions of one operand type (right and left) of several updates in one launch,
+// and the fixed-order sums of several in another (see launch_reduce): the descriptor tables
+// built on the host, the launch from tables already staged on the device, so that a caller
+// can stage the tables of many launches in one copy.  Results are bitwise those of
+// launch_gemm and launch_reduce on each.
 struct BatchedGemm {
   std::vector<GemmTask> tasks;
   int64_t blocks = 0;
@@ -296,7 +294,6 @@ void copy_layout(const double* src, void* out, int dt, int64_t d0, int64_t d1, i
                  int64_t s2, int cdim, int64_t lim, hipStream_t stream);
 
 // ---------------------------------------------------------------- small utilities
-void launch_zero(double* p, int64_t n, hipStream_t stream);
 // Several FP64 arrays in one launch: zero them, or set *flag when one holds a non-finite value.
 struct SegList {
   static constexpr int kMax = 2 * TTNN_MAX_NODES + 1;    // two arrays per node plus the root's
@@ -316,10 +313,7 @@ void launch_finite_list(const SegList& s, int* flag, hipStream_t stream);
 // Workgroups of a list launch: one for every 256 entries of an array, kSegBlocks at most
 constexpr int kSegBlocks = 512;
 int list_blocks(const SegList& s);
-void launch_axpy(double* y, const double* x, double alpha, int64_t n, hipStream_t stream);
 void launch_copy_f64(double* dst, const double* src, int64_t n, hipStream_t stream);
-void launch_f64_to_f32(float* dst, const double* src, int64_t n, hipStream_t stream);
-void launch_finite_check(const double* p, int64_t n, int* flag, hipStream_t stream);
 void launch_zero_int(int* p, int64_t n, hipStream_t stream);
 
 // ---------------------------------------------------------------- recovery phase

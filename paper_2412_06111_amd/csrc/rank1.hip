@@ -19,17 +19,6 @@ namespace {
 constexpr int kThreadsR = 256;
 constexpr int kFacCache = 2048;   // factor entries of a term group kept in LDS by the GEMV (16 KB)
 
-__device__ inline double kron_weight(const KronVec& kv, int64_t row) {
-  double w = 1.0;
-  for (int p = 0; p < kv.n; ++p) {
-    const int64_t e = kv.len[p];
-    const int64_t i = row % e;
-    row /= e;
-    w *= kv.v[p][i];
-  }
-  return w;
-}
-
 // partial[(y nb + b) ncols + j] = sum over the rows of block b of D[row * ncols + j] *
 // weight_y(row), for the terms y of the batch.  The block's rows are contiguous in D:
 // each step copies RB of them into LDS with 16-byte loads (rows padded by one element
