@@ -264,7 +264,9 @@ __device__ __forceinline__ void tile_of(const SttnnArgs& a, int& tA, int& tB) {
   }
 }
 
-// The FP32 forms at r = 32 whose products are split into BF16 ones (sttnn_t4_x3_kernel).
+// The FP32 forms at r = 32 whose products are split into BF16 ones (sttnn_t4_x3_kernel).  At
+// r = 64 the Y_A planes of two slabs (147 KB) leave no room for the stages of T; at r = 16 the
+// STTNN form contracts Z1 in the tile, and the TTNN form was left as it was.
 constexpr bool split_form(int dt, int R, bool tt, bool zout) { return dt == TTNN_F32 && R == 32 && (tt || zout); }
 
 // ZO (STTNN only): instead of contracting Z1 with X_2 in the tile (which re-reads the
@@ -1171,7 +1173,8 @@ __global__ __launch_bounds__(kThreadsF) void sttnn_t4_x3_kernel(SttnnArgs a) {
 // every sub-tile reads stay where they are used: the Y_A rows of the tile's two slabs in LDS
 // (96 KB, beside two 32 KB stages of T), Y_1 in the registers of waves 2, 3 (192 a lane).
 // X_A and X_1 go from global memory to the registers of waves 4-7, each value right after its
-// last product for its next use, a sub-tile on.  Waves 0, 1, which load nothing else, copy
+// last product for its next use, a sub-tile on.  (At r = 64 the Y_A rows of two slabs are 192
+// KB.)  Waves 0, 1, which load nothing else, copy
 // the slab a sub-tile ahead.
 // 128^4, r = 32: the sweep 2450 -> 1495 us in sttnn_t4_kernel's place (one phase for (b)/(d1)
 // and one for (a)/(c), the matrix cores 47% busy; now 85%, at the 2.07 GHz that the card

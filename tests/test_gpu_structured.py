@@ -255,3 +255,26 @@ def test_contraction_order(P, s, r):
         for j in sorted({0, r // 2, r - 1}):
             assert got[o, j] == _contracted_in_order(core, (X[1], X[2]), (s, s, s), r, o, j), (o, j)
     plan.close()
+
+
+@pytest.mark.parametrize("spec,n,s,r", [(O.T4, 60, 43, 27), (O.T5, 71, 59, 28)], ids=["t4", "t5"])
+def test_rounding_cores_to_their_conditioning(P, spec, n, s, r):
+    """Cores of roundings with a two-child root, the worst conditioned ones (1 / i^2 decay),
+    against the oracle's.  A core is a product of sketches, factors Q of the children's Omega
+    and Omega^+, so it moves by the sketches' relative errors (sums of some 10^3 to 10^5 FP64
+    products, 64 x 2^-53 in norm) times the largest condition number of an Omega."""
+    d, p = len([m for m in W.tree_spec_nodes(spec) if len(m[1]) == 1]), 10
+    cores = W.decaying_ttn_cores(spec, (n,) * d, s, 1.0 / np.arange(1, s + 1) ** 2, seed=3)
+    tree = O.Tree(spec, (n,) * d, r, p)
+    X, Y = S.factors(2, (n,) * d, r, p)
+    want = S.ttn_sketch(cores, tree, X, Y)
+    kappa = max(np.linalg.cond(want["Omega"][t.id]) for t in tree.nodes if t.id)
+    oc, _ = O.assemble(want, tree)
+    ocm = oracle_cores_by_modes(tree, oc)
+    plan = P.Plan(spec, (n,) * d, r, p, variant="kr", seed=2)
+    plan.update_ttn(dev_cores(cores), s)
+    hc = host_cores(plan, plan.assemble())
+    errs = {m: errs2(hc[m], ocm[m])[0] for m in ocm}
+    print(f"condition {kappa:.2e}, bound {64 * 2.0 ** -53 * kappa:.2e}, errors {errs}", flush=True)
+    assert max(errs.values()) <= 64 * 2.0 ** -53 * kappa
+    plan.close()
