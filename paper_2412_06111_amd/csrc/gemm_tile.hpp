@@ -25,7 +25,7 @@ namespace ttnn {
 // out one a thread and kept in LDS.  A form that divided in 64 bits for every entry and
 // worked out a step's DRM rows on 16 threads took 2.5 us for a step of 16 values; now a
 // wave issues ~60 vector instructions beside the 16 MFMAs of a 64 x 32 x 32 step, and the
-// tile is bound by those two and the barrier between steps (MFMA busy 37% and 40% in the two
+// tile is bound by those two and the barrier between steps (MFMA busy 40% and 37% in the two
 // workloads below).  Measured
 // with it before and now: a whole 97 x 113 x 61 x 75 FP32 tensor (r = 21, TTNN) 1250 ->
 // 500 us (a pass over the 200 MB 140-220 -> 55-90 us); a 33.9M-entry box of a 64^5 FP32

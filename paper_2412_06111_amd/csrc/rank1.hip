@@ -280,8 +280,8 @@ void launch_gemv_dt(const TD* D, int64_t rows, int ncols, const KronBatch& kb, i
 // be split over S workgroups instead.  A term's row of the product does not depend on the
 // other rows, so its partials are the same in any batch.
 //
-// Bound by the map's bytes: a 64^5 leaf map (64^4 x 24 FP32, 1.61 GB, 16 terms) takes 350 us,
-// 4.6 TB/s (the products alone 165 us at the FP64 MFMA's rate); through LDS tiles with a
+// Bound by the map's bytes: a 64^5 leaf map (64^4 x 24 FP32, 1.61 GB, 16 terms) takes 365 us,
+// 4.4 TB/s (the products alone 165 us at the FP64 MFMA's rate); through LDS tiles with a
 // guard an entry and no pairing it took 530 us.  A group of 16 terms on 64^5: 3390 -> 1976
 // us, with the wide maps (36 columns) here too (417 -> 24 us) and the outer products in
 // one launch.
